@@ -56,20 +56,25 @@
 // nothing but the exponent range, which the limit bounds.  No per-tile row
 // max is computed on the common path.
 //
-// K and V tiles each live in a 4-entry LDS ring (slot = tile mod 4), and
-// iteration j reads K(j+1) and V(j-1).  With head_dim 128 the tiles go from
-// memory straight into LDS (buffer loads with the LDS flag, swizzled rows
-// instead of padded ones, 64 KiB of LDS): the even iteration of each pair
-// issues the loads of K(j+3), K(j+4), V(j+1) and V(j+2), and the pair ends
-// with one barrier after they have landed.  With head_dim 64 the tiles are
-// staged through registers: iteration j writes K(j+3) and V(j+1) loaded in
-// iteration j-1 and loads K(j+4) and V(j+2).  Either way a tile is in place
-// at least a barrier before it is read and only every second iteration ends
-// with a workgroup barrier (one that lets global loads meant for later
-// iterations stay in flight), which halves the barrier waits and lets the
-// waves drift apart by up to an iteration.  The loop is unrolled so that
-// the ring slots, the barrier placement and the score registers are fixed
-// at compile time.
+// K and V tiles (8 KiB: 32 keys at head_dim 128, 64 at 64) each live in a
+// 4-entry LDS ring (slot = tile mod 4), and iteration j reads K(j+1) and
+// V(j-1).  The tiles go from memory straight into LDS (buffer loads with the
+// LDS flag, swizzled rows instead of padded ones, 64 KiB of LDS): the even
+// iteration of each pair issues the loads of K(j+3), K(j+4), V(j+1) and
+// V(j+2), and the pair ends with one barrier after they have landed.  A tile
+// is in place at least a barrier before it is read and only every second
+// iteration ends with a workgroup barrier (one that lets global loads meant
+// for later iterations stay in flight), which halves the barrier waits and
+// lets the waves drift apart by up to an iteration.  The loop is unrolled so
+// that the ring slots, the barrier placement and the score registers are
+// fixed at compile time.
+//
+// At head_dim 64 a score carries half the MFMA work and the same vector
+// work, so the loop is bound by the latter: per 64-key tile and SIMD about
+// 1660 cycles of vector issue (FMA, exponential, add, half a pack per score)
+// against 1024 of MFMAs.  The 64-key tile halves the barriers, loads and
+// address arithmetic per score; against 32-key tiles staged through
+// registers a 32/8-head call of P=8192, N=512 takes 45.2 us instead of 48.0.
 #include "sc_internal.h"
 
 #include <cmath>
@@ -109,27 +114,31 @@ __device__ __forceinline__ T load_const(const T *p) {
 constexpr int kThreads = 512;            // 8 waves, 2 per SIMD
 constexpr int KT = kAttnKeyTile;
 static_assert(kAttnRows == 8 * 32, "eight waves of 32 rows");
-static_assert(KT == 32, "one 32-key MFMA block per tile");
+static_assert(KT == 32, "key ranges are cut at MFMA block boundaries");
 
 // 32x32 MFMA accumulator layout: element r of lane l holds C[m][n] with
 // n = l % 32 and m = 8 * (r / 4) + 4 * (l / 32) + r % 4.
 __device__ __forceinline__ int acc_m(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
+// One K or V tile: 8 KiB of key rows of one KV head, i.e. 32 keys at
+// head_dim 128 and 64 at head_dim 64, so that an iteration of the loop has
+// 16 MFMAs and one load into LDS per wave and operand at either head_dim.
 template <int D>
-struct Geo {
-  static constexpr int kChunksPerRow = D / 8;                     // 16-byte chunks per key row
-  static constexpr int kTileChunks = KT * kChunksPerRow;          // chunks of K (or V) per tile
-  static constexpr int kChunksPerThread = 2 * kTileChunks / kThreads;  // K and V of one tile over the workgroup
-  // K rows: 16-byte reads of 16 consecutive keys fall on disjoint banks.
-  static constexpr int kLdsK = D + 8;
-  // V rows: the 8 rows of one transpose read (64 bytes each) fall on
-  // disjoint bank ranges (row stride = 16 dwords mod 64).
-  static constexpr int kLdsV = D + 32;
-  static constexpr int kTileK = KT * kLdsK;
-  static constexpr int kTileV = KT * kLdsV;
-  static constexpr int kSlots = 4;   // ring entries per operand (K and V)
-  static constexpr int kSmem = kSlots * (kTileK + kTileV);
-  static_assert(kChunksPerThread * kThreads == 2 * kTileChunks, "tile split");
+struct Tile {
+  static constexpr int kRowBytes = D * 2;
+  static constexpr int kSlotBytes = 8192;
+  static constexpr int kKeys = kSlotBytes / kRowBytes;
+  static constexpr int kBlocks = kKeys / 32;               // 32-key MFMA blocks of the S^T product
+  static constexpr int kChunksPerRow = kRowBytes / 16;
+  static constexpr int kRowsPerLoad = 1024 / kRowBytes;    // key rows of one wave's load (64 lanes x 16 B)
+  static_assert(8 * kRowsPerLoad == kKeys, "eight waves load a tile");
+  // LDS rows are unpadded; chunk c (16 B) of row r sits at position
+  // c ^ swz_k(r) (K) or c ^ swz_v(r) (V).  K fragment reads take one chunk
+  // of 16 consecutive rows, V transpose reads 64 bytes of 4 consecutive
+  // rows: with these, each covers all 64 banks once (256 bytes = one row at
+  // head_dim 128, two at 64).
+  static __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+  static __device__ __forceinline__ int swz_v(int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
 };
 
 // Element type of q, K, V, the probabilities of the PV product and the
@@ -193,21 +202,9 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 
-// Workgroup barrier that orders LDS only: this wave's LDS accesses complete
-// before it, global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// head_dim 128: K/V ring slots loaded straight into LDS (see attn_item).
+// K/V ring slots, loaded straight into LDS (see attn_item).
 // One array per slot and operand, so the compiler can tell that a load in
 // flight into one slot does not alias reads of another and needs no wait.
-struct DmaGeo {
-  static constexpr int kRowBytes = 128 * 2;               // one key row of one KV head
-  static constexpr int kSlotBytes = KT * kRowBytes;        // one tile, 8 KiB
-};
 // Pairs of iterations a tile load has to land in, and the ring size that
 // allows (tiles read in the A pairs after a load plus the two it loads).
 // One pair is enough: with two or three (96 or 128 KiB of LDS) the kernel
@@ -216,8 +213,8 @@ constexpr int kDmaAhead = 1;
 constexpr int kDmaRing = 2 * kDmaAhead + 2;
 static_assert(kDmaAhead >= 1 && kDmaRing <= 8, "ring of at most 8 slots");
 #define SC_DMA_SLOT(n)                                                          \
-  __shared__ __attribute__((aligned(1024))) unsigned char dma_k##n[DmaGeo::kSlotBytes]; \
-  __shared__ __attribute__((aligned(1024))) unsigned char dma_v##n[DmaGeo::kSlotBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char dma_k##n[Tile<128>::kSlotBytes]; \
+  __shared__ __attribute__((aligned(1024))) unsigned char dma_v##n[Tile<128>::kSlotBytes];
 SC_DMA_SLOT(0)
 SC_DMA_SLOT(1)
 SC_DMA_SLOT(2)
@@ -272,74 +269,46 @@ __device__ __forceinline__ void dma_wait_all() {
   asm volatile("" ::: "memory");
 }
 
-// S^T(tile) = K_tile . Q^T: D / 16 dependent MFMAs.
-template <int D, int DT>
-__device__ __forceinline__ void qk_tile(const uint16_t *sk, const u32x4 (&qf)[D / 16], f32x16 &s, int lane) {
-  using G_ = Geo<D>;
+// Masks keys past a row's last visible key: element r of block b holds key
+// offset 32 b + acc_m(r, half) within the tile, and lim is the row's last
+// visible offset minus 4 half.
+template <int NB>
+__device__ __forceinline__ void apply_mask(f32x16 (&s)[NB], int lim) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) s[r] = 0.f;
-  const uint16_t *krow = sk + (lane & 31) * G_::kLdsK + 8 * (lane >> 5);
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
-  for (int k = 0; k < D / 16; ++k)
-    s = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(krow + 16 * k), qf[k], s);
+    for (int r = 0; r < 16; ++r)
+      if (32 * b + acc_m(r, 0) > lim) s[b][r] = -INFINITY;
 }
 
-// O^T += V^T . P^T.  MFMA step t covers keys 16 t + [0, 16); k-slot e of a
-// lane in half `half` holds key 16 t + 4 half + (e < 4 ? e : e + 4), which
-// is accumulator element 8 t + e of S^T, i.e. pf[t] element e.
-template <int D, int DT>
-__device__ __forceinline__ void pv_tile(const uint16_t *sv, const u32x4 (&pf)[2], f32x16 (&oacc)[D / 32],
-                                        int lane) {
-  using G_ = Geo<D>;
-  constexpr int NC = D / 32;
-  const int tr_row = 4 * (lane >> 5) + ((lane & 15) >> 2);
-  const int tr_dim = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const uint16_t *vb = sv + tr_row * G_::kLdsV + tr_dim;
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const uint16_t *p = vb + 16 * t * G_::kLdsV + 32 * c;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 8 * G_::kLdsV));
-      u32x4 vw;
-      vw[0] = __builtin_bit_cast(u32x2, lo)[0];
-      vw[1] = __builtin_bit_cast(u32x2, lo)[1];
-      vw[2] = __builtin_bit_cast(u32x2, hi)[0];
-      vw[3] = __builtin_bit_cast(u32x2, hi)[1];
-      oacc[c] = Elem<DT>::mfma(vw, pf[t], oacc[c]);
-    }
-}
-
-// Masks keys past a row's last visible key: element r holds key offset
-// acc_m(r, half) within the tile, and lim is the row's last visible offset
-// minus 4 half.
-__device__ __forceinline__ void apply_mask(f32x16 &s, int lim) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if (acc_m(r, 0) > lim) s[r] = -INFINITY;
-}
-
-// Row max of sl2 * s over the tile's 32 keys (both wave halves); -inf when
+// Row max of sl2 * s over the tile's keys (both wave halves); -inf when
 // every key of the row is masked.
-__device__ __forceinline__ float tile_max(const f32x16 &s, float sl2) {
-  float m4[4];
+template <int NB>
+__device__ __forceinline__ float tile_max(const f32x16 (&s)[NB], float sl2) {
+  float m4[4 * NB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) m4[i] = fmaxf(fmaxf(s[4 * i], s[4 * i + 1]), fmaxf(s[4 * i + 2], s[4 * i + 3]));
-  return max_with_other_half(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]))) * sl2;
+  for (int i = 0; i < 4 * NB; ++i) {
+    const f32x16 &x = s[i >> 2];
+    const int r = 4 * (i & 3);
+    m4[i] = fmaxf(fmaxf(x[r], x[r + 1]), fmaxf(x[r + 2], x[r + 3]));
+  }
+  float m = m4[0];
+#pragma unroll
+  for (int i = 1; i < 4 * NB; ++i) m = fmaxf(m, m4[i]);
+  return max_with_other_half(m) * sl2;
 }
 
-// p = exp2(sl2 * s - m) for this lane's 16 keys, packed to the element type,
+// p = exp2(sl2 * s - m) for this lane's keys, packed to the element type,
 // and their fp32 sum (two chains).
-template <int DT>
-__device__ __forceinline__ float softmax_tile(const f32x16 &s, u32x4 (&pf)[2], float sl2, float m) {
+template <int DT, int NB>
+__device__ __forceinline__ float softmax_tile(const f32x16 (&s)[NB], u32x4 (&pf)[2 * NB], float sl2, float m) {
   float r2[2] = {0.f, 0.f};
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < 2 * NB; ++t)
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
-      const float x0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * t + e], sl2, -m));
-      const float x1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * t + e + 1], sl2, -m));
+      const float x0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t >> 1][8 * (t & 1) + e], sl2, -m));
+      const float x1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t >> 1][8 * (t & 1) + e + 1], sl2, -m));
       pf[t][e >> 1] = Elem<DT>::pack(x0, x1);
       r2[0] += x0;
       r2[1] += x1;
@@ -351,9 +320,8 @@ template <int D>
 struct WaveState {
   u32x4 qf[D / 16];   // raw 16-bit patterns
   f32x16 oacc[D / 32];
-  f32x16 s[2];        // raw scores of the even / odd tiles
-  u32x4 pf_prev[2];   // P(j-1) for the PV product (head_dim 64 loop)
-  u32x4 pfb[2][2];    // P of the even / odd tiles (head_dim 128 loop: no copy per tile)
+  f32x16 s[2][Tile<D>::kBlocks];       // raw scores of the even / odd tiles
+  u32x4 pfb[2][2 * Tile<D>::kBlocks];  // P of the even / odd tiles (no copy per tile)
   float m_run;        // reference max of sl2 * s, log2 units (0 until a key is visible)
   float l_run;        // this lane's share of the denominator
 };
@@ -363,7 +331,8 @@ struct WaveState {
 // and O (O already holds PV(j-1), computed against the old reference), and
 // redo the tile's exponentials.  Returns the new tile sum.
 template <int D, int DT>
-__device__ __forceinline__ float settle_max(WaveState<D> &w, const f32x16 &s, u32x4 (&pf)[2], float sl2) {
+__device__ __forceinline__ float settle_max(WaveState<D> &w, const f32x16 (&s)[Tile<D>::kBlocks],
+                                            u32x4 (&pf)[2 * Tile<D>::kBlocks], float sl2) {
   const float m_new = fmaxf(w.m_run, tile_max(s, sl2));
   const float corr = __builtin_amdgcn_exp2f(w.m_run - m_new);
   w.m_run = m_new;
@@ -410,9 +379,10 @@ __device__ __forceinline__ void store_row(const WaveState<D> &w, float inv, int 
 // cache; the two kinds of item are separate copies of the whole body so that
 // each is register-allocated on its own.
 template <int D, int DT, bool kPaged>
-__device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi, uint16_t *smem) {
-  using G_ = Geo<D>;
-  constexpr int NCH = G_::kChunksPerThread;
+__device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi) {
+  using G_ = Tile<D>;
+  constexpr int NB = G_::kBlocks;
+  constexpr int TK = G_::kKeys;      // keys per tile
   // Scalar loads (see load_const), so the key-range and address arithmetic
   // built from the record stays in scalar registers.
   const SeqDesc sd = a.seqs != nullptr ? load_const(a.seqs + wi.seq) : a.seq0;
@@ -461,28 +431,20 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
   const int64_t kv_stride = (int64_t)a.n_kv_heads * D;
   const int k_begin = wi.k_begin;
   const int k_end = wi.k_end;
-  const int n = (k_end - k_begin + KT - 1) / KT;
+  const int n = (k_end - k_begin + TK - 1) / TK;
   const int64_t first_row = ((int64_t)sd.cu_k + k_begin) * kv_stride + (int64_t)wi.kvh * D;
   const uint16_t *const kb = a.k + first_row;
   const uint16_t *const vb = a.v + first_row;
   // Byte counts, also of the tiles loaded past the end, fit in 31 bits
   // (checked on the host).
   const uint32_t range_bytes = (uint32_t)((((int64_t)(k_end - k_begin) - 1) * kv_stride + D) * 2);
-  const uint32_t tile_bytes = (uint32_t)(KT * kv_stride * 2);
-  // Signed 32-bit offset arithmetic stays on the scalar unit (an unsigned
-  // saturating subtract would be a vector instruction plus a readfirstlane).
-  auto rsrc = [&](const uint16_t *base, int t) {
-    const int off = t * (int)tile_bytes;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(base) + off),
-                                             (short)0, max((int)range_bytes - off, 0), 0x00020000);
-  };
-
+  const uint32_t tile_bytes = (uint32_t)(TK * kv_stride * 2);
   // First tile that needs the mask, the same for the whole workgroup: it
   // reaches past the key range or past the diagonal of the first query.
   const int diag0 = sd.prefix + wi.q0;
-  const int j_mask = max(0, min(n, (min(k_end, diag0 + 1) - k_begin) / KT));
+  const int j_mask = max(0, min(n, (min(k_end, diag0 + 1) - k_begin) / TK));
   const int my_last = min(k_end - 1, sd.prefix + qpos);
-  auto lim_of = [&](int j) { return my_last - (k_begin + j * KT) - 4 * half; };
+  auto lim_of = [&](int j) { return my_last - (k_begin + j * TK) - 4 * half; };
 
   // Device-side dependency on the copy stream (see AttnArgs::ready_flag).
   // The poll is a relaxed device-scope load (no cache invalidation per
@@ -514,404 +476,263 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
     timed_out = s_timeout != 0;
   }
 
-  if constexpr (D == 128) {
-    // K and V tiles go from memory straight into LDS (buffer loads with the
-    // LDS flag; no staging registers).  Wave w loads rows 4 w .. 4 w + 3 of
-    // every K and V tile: one 16-byte load per lane and operand, lane i
-    // filling bytes 16 i .. 16 i + 15 of the wave's four rows.  Rows are
-    // unpadded (256 bytes); chunk c of K row r sits at position c ^ (r mod 16)
-    // and of V row r at c ^ 4 (r mod 4), which keeps the K fragment reads and
-    // the V transpose reads free of bank conflicts.  Each lane loads the
-    // chunk that belongs at its position.
-    const int row_bytes = (int)(kv_stride * 2);
-    const int l4 = lane >> 4;
-    const int p16 = lane & 15;
-    const int my_row = 4 * wave;
-    const int voff_k = l4 * row_bytes + ((p16 ^ (4 * (wave & 3) + l4)) << 4);
-    const int voff_v = l4 * row_bytes + ((p16 ^ (l4 << 2)) << 4);
-    // This lane's LDS read offsets within a slot: K fragment k (row col,
-    // chunk 2 k + half) and the transpose read of dim block c (key row
-    // tr_row; the other key rows of the product are immediates).
-    int k_rd[D / 16], v_rd[D / 32];
+  // K and V tiles go from memory straight into LDS (buffer loads with the
+  // LDS flag; no staging registers).  Wave w loads kRowsPerLoad consecutive
+  // rows of every K and V tile: one 16-byte load per lane and operand, lane
+  // i filling bytes 16 i .. 16 i + 15 of the wave's rows.  Rows are unpadded
+  // and swizzled (see Tile), which keeps the K fragment reads and the V
+  // transpose reads free of bank conflicts: each lane loads the chunk that
+  // belongs at its position.
+  const int row_bytes = (int)(kv_stride * 2);
+  const int my_row = G_::kRowsPerLoad * wave;
+  int voff_k, voff_v;
+  {
+    const int r = lane / G_::kChunksPerRow;
+    const int c = lane % G_::kChunksPerRow;
+    voff_k = r * row_bytes + ((c ^ G_::swz_k(my_row + r)) << 4);
+    voff_v = r * row_bytes + ((c ^ G_::swz_v(my_row + r)) << 4);
+  }
+  // This lane's LDS read offsets within a slot: K fragment k of block 0
+  // (row col, chunk 2 k + half) and the transpose read of dim block c (key
+  // row tr_row; the other blocks and key rows of the product are
+  // immediates, as the swizzles repeat every 16 rows).
+  int k_rd[D / 16], v_rd[D / 32];
 #pragma unroll
-    for (int k = 0; k < D / 16; ++k) k_rd[k] = col * DmaGeo::kRowBytes + (((2 * k + half) ^ (col & 15)) << 4);
-    {
-      const int tr_row = 4 * half + ((lane & 15) >> 2);
-      const int lo = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-      const int x = (lane >> 2) & 3;
+  for (int k = 0; k < D / 16; ++k) k_rd[k] = col * G_::kRowBytes + (((2 * k + half) ^ G_::swz_k(col)) << 4);
+  {
+    const int tr_row = 4 * half + ((lane & 15) >> 2);
+    const int lo = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
 #pragma unroll
-      for (int c = 0; c < D / 32; ++c) v_rd[c] = tr_row * DmaGeo::kRowBytes + ((4 * (c ^ x) + lo) << 4) + 8 * (lane & 1);
+    for (int c = 0; c < D / 32; ++c)
+      v_rd[c] = tr_row * G_::kRowBytes + (((4 * c + lo) ^ G_::swz_v(tr_row)) << 4) + 8 * (lane & 1);
+  }
+  // Regular-cache item: key k of the sequence is row k mod B of local
+  // block rc_ids[rc_off + k / B], read in place.  A wave's rows start on a
+  // multiple of their count (4 or 8) and B >= 16 is a power of two, so they
+  // share one block; its index is a scalar load (the table is read through the
+  // constant address space: the host writes it before the launch), made a
+  // pair of iterations before the tile's data load.
+  const __attribute__((address_space(4))) int32_t *rc_ids_c =
+      kPaged ? (const __attribute__((address_space(4))) int32_t *)(a.rc_ids + sd.rc_off) : nullptr;
+  // This KV head's K and V rows in block 0 of the layer; block b is
+  // b * rc_block_bytes further (under 4 GiB, checked on the host), so the
+  // per-tile address is a 32 x 32 -> 64-bit product and two adds.
+  const char *rc_kbase =
+      kPaged ? reinterpret_cast<const char *>(a.rc_base + a.rc_layer_elems + (int64_t)wi.kvh * D) : nullptr;
+  const char *rc_vbase = kPaged ? rc_kbase + a.rc_half_elems * 2 : nullptr;
+  const uint32_t rc_block_bytes = kPaged ? (uint32_t)(a.rc_block_elems * 2) : 0u;
+  const int rc_mask = (1 << a.block_shift) - 1;
+  auto blk_of = [&](int t) -> int {
+    if constexpr (!kPaged) {
+      return 0;
+    } else {
+      return rc_ids_c[min(k_begin + t * TK + my_row, k_end - 1) >> a.block_shift];
     }
-    // Regular-cache item: key k of the sequence is row k mod B of local
-    // block rc_ids[rc_off + k / B], read in place.  A wave's four rows start
-    // on a multiple of 4 and B >= 16 is a power of two, so they share one
-    // block; its index is a scalar load (the table is read through the
-    // constant address space: the host writes it before the launch), made a
-    // pair of iterations before the tile's data load.
-    const __attribute__((address_space(4))) int32_t *rc_ids_c =
-        kPaged ? (const __attribute__((address_space(4))) int32_t *)(a.rc_ids + sd.rc_off) : nullptr;
-    // This KV head's K and V rows in block 0 of the layer; block b is
-    // b * rc_block_bytes further (under 4 GiB, checked on the host), so the
-    // per-tile address is a 32 x 32 -> 64-bit product and two adds.
-    const char *rc_kbase =
-        kPaged ? reinterpret_cast<const char *>(a.rc_base + a.rc_layer_elems + (int64_t)wi.kvh * D) : nullptr;
-    const char *rc_vbase = kPaged ? rc_kbase + a.rc_half_elems * 2 : nullptr;
-    const uint32_t rc_block_bytes = kPaged ? (uint32_t)(a.rc_block_elems * 2) : 0u;
-    const int rc_mask = (1 << a.block_shift) - 1;
-    auto blk_of = [&](int t) -> int {
-      if constexpr (!kPaged) {
-        return 0;
-      } else {
-        return rc_ids_c[min(k_begin + t * KT + my_row, k_end - 1) >> a.block_shift];
-      }
-    };
-    // This wave's four rows of tile t, K (kV false) or V, into `slot`.  The
-    // buffer resource ends after the last row of the item's range (of the
-    // block, for a regular-cache item), so rows past it, and whole tiles
-    // past the last one, load zeros without touching memory.
-    auto dma = [&](unsigned char *slot, int t, auto v_tag, int blk) {
-      constexpr bool kV = decltype(v_tag)::value;
-      const int key = k_begin + t * KT + my_row;
-      const char *base;
-      int range;
-      if constexpr (kPaged) {
-        const int rib = min(key, k_end - 1) & rc_mask;   // first row within the block
-        const int rows = min(rc_mask + 1 - rib, k_end - key);
-        base = (kV ? rc_vbase : rc_kbase) + (uint64_t)(uint32_t)blk * rc_block_bytes + (uint32_t)(rib * row_bytes);
-        range = rows > 0 ? ((rows - 1) * row_bytes + 2 * D) : 0;
-      } else {
-        // Signed 32-bit offsets (the host keeps a sequence's keys, plus the
-        // tiles loaded past its end, under 2^31 bytes): a subtract and a max
-        // on the scalar unit.  A 64-bit compare would be a vector
-        // instruction whose result the scalar select then waits for (~2%
-        // of the loop), as would a saturating unsigned subtract.
-        const int off = t * (int)tile_bytes + my_row * row_bytes;
-        base = reinterpret_cast<const char *>(kV ? vb : kb) + off;
-        range = max((int)range_bytes - off, 0);
-      }
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<char *>(base), (short)0, __builtin_amdgcn_readfirstlane(range), 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(slot + my_row * DmaGeo::kRowBytes), 16,
-                                               kV ? voff_v : voff_k, 0, 0, 0);
-    };
-    auto qk = [&](const unsigned char *slot, f32x16 &s) {
+  };
+  // This wave's rows of tile t, K (kV false) or V, into `slot`.  The
+  // buffer resource ends after the last row of the item's range (of the
+  // block, for a regular-cache item), so rows past it, and whole tiles
+  // past the last one, load zeros without touching memory.
+  auto dma = [&](unsigned char *slot, int t, auto v_tag, int blk) {
+    constexpr bool kV = decltype(v_tag)::value;
+    const int key = k_begin + t * TK + my_row;
+    const char *base;
+    int range;
+    if constexpr (kPaged) {
+      const int rib = min(key, k_end - 1) & rc_mask;   // first row within the block
+      const int rows = min(rc_mask + 1 - rib, k_end - key);
+      base = (kV ? rc_vbase : rc_kbase) + (uint64_t)(uint32_t)blk * rc_block_bytes + (uint32_t)(rib * row_bytes);
+      range = rows > 0 ? ((rows - 1) * row_bytes + 2 * D) : 0;
+    } else {
+      // Signed 32-bit offsets (the host keeps a sequence's keys, plus the
+      // tiles loaded past its end, under 2^31 bytes): a subtract and a max
+      // on the scalar unit.  A 64-bit compare would be a vector
+      // instruction whose result the scalar select then waits for (~2%
+      // of the loop), as would a saturating unsigned subtract.
+      // At head_dim 64 the tiles past the end would reach further than that
+      // margin: they all load from the first one, past the range as well.
+      const int off = (NB == 1 ? t : min(t, n)) * (int)tile_bytes + my_row * row_bytes;
+      base = reinterpret_cast<const char *>(kV ? vb : kb) + off;
+      range = max((int)range_bytes - off, 0);
+    }
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char *>(base), (short)0, __builtin_amdgcn_readfirstlane(range), 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(slot + my_row * G_::kRowBytes), 16,
+                                             kV ? voff_v : voff_k, 0, 0, 0);
+  };
+  auto qk = [&](const unsigned char *slot, f32x16 (&s)[NB]) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int k = 0; k < D / 16; ++k)
-        s = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(slot + k_rd[k]), w.qf[k], s);
-    };
-    // O^T += V^T . P^T, operands as in pv_tile.
-    auto pv = [&](const unsigned char *slot, const u32x4 (&pfp)[2]) {
+        s[b] = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(slot + k_rd[k] + 32 * b * G_::kRowBytes), w.qf[k],
+                              k == 0 ? f32x16{} : s[b]);
+  };
+  // V^T operand of PV step (t, c): dims 32 c .. 32 c + 31 of keys
+  // 16 t + [0, 16); k-slot e of a lane in half `half` holds key
+  // 16 t + 4 half + (e < 4 ? e : e + 4), which is accumulator element
+  // 8 (t mod 2) + e of S^T block t / 2, i.e. pf[t] element e.
+  auto v_operand = [&](const unsigned char *slot, int t, int c) -> u32x4 {
+    const unsigned char *p = slot + v_rd[c] + 16 * t * G_::kRowBytes;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 8 * G_::kRowBytes));
+    u32x4 vw;
+    vw[0] = __builtin_bit_cast(u32x2, lo)[0];
+    vw[1] = __builtin_bit_cast(u32x2, lo)[1];
+    vw[2] = __builtin_bit_cast(u32x2, hi)[0];
+    vw[3] = __builtin_bit_cast(u32x2, hi)[1];
+    return vw;
+  };
+  // O^T += V^T . P^T.
+  auto pv = [&](const unsigned char *slot, const u32x4 (&pfp)[2 * NB]) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2 * NB; ++t)
 #pragma unroll
-        for (int c = 0; c < D / 32; ++c) {
-          const unsigned char *p = slot + v_rd[c] + 16 * t * DmaGeo::kRowBytes;
-          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 8 * DmaGeo::kRowBytes));
-          u32x4 vw;
-          vw[0] = __builtin_bit_cast(u32x2, lo)[0];
-          vw[1] = __builtin_bit_cast(u32x2, lo)[1];
-          vw[2] = __builtin_bit_cast(u32x2, hi)[0];
-          vw[3] = __builtin_bit_cast(u32x2, hi)[1];
-          w.oacc[c] = Elem<DT>::mfma(vw, pfp[t], w.oacc[c]);
-        }
-    };
+      for (int c = 0; c < D / 32; ++c) w.oacc[c] = Elem<DT>::mfma(v_operand(slot, t, c), pfp[t], w.oacc[c]);
+  };
 
-    if (n > 0 && !timed_out) {
-      using T = std::true_type;
-      using F = std::false_type;
-      constexpr int A = kDmaAhead;
-      constexpr int R = kDmaRing;
-      // Regular-cache block indices of the tiles the current pair loads into
-      // K (bk0, bk1) and V (bv0, bv1), and of the next pair's K tiles.  The
-      // V tiles of a pair are the K tiles of the pair before.
-      int bv0 = blk_of(2 * A - 1), bv1 = blk_of(2 * A), bk0 = blk_of(2 * A + 1), bk1 = blk_of(2 * A + 2);
-      int bn0 = 0, bn1 = 0;
-      // Prologue: K(0 .. 2A) and V(0 .. 2A-2), the operands of the first A
-      // pairs; then QK(0).  The first pair loads into the slot QK(0) reads:
-      // a second barrier.
-      static_for<0, 2 * A + 1>([&](auto t) { dma(dma_k_slot<decltype(t)::value % R>(), t, F(), blk_of(t)); });
-      static_for<0, 2 * A - 1>([&](auto t) { dma(dma_v_slot<decltype(t)::value % R>(), t, T(), blk_of(t)); });
-      dma_barrier<0>();
-      qk(dma_k_slot<0>(), w.s[0]);
-      dma_barrier<0>();
+  if (n > 0 && !timed_out) {
+    using T = std::true_type;
+    using F = std::false_type;
+    constexpr int A = kDmaAhead;
+    constexpr int R = kDmaRing;
+    // Regular-cache block indices of the tiles the current pair loads into
+    // K (bk0, bk1) and V (bv0, bv1), and of the next pair's K tiles.  The
+    // V tiles of a pair are the K tiles of the pair before.
+    int bv0 = blk_of(2 * A - 1), bv1 = blk_of(2 * A), bk0 = blk_of(2 * A + 1), bk1 = blk_of(2 * A + 2);
+    int bn0 = 0, bn1 = 0;
+    // Prologue: K(0 .. 2A) and V(0 .. 2A-2), the operands of the first A
+    // pairs; then QK(0).  The first pair loads into the slot QK(0) reads:
+    // a second barrier.
+    static_for<0, 2 * A + 1>([&](auto t) { dma(dma_k_slot<decltype(t)::value % R>(), t, F(), blk_of(t)); });
+    static_for<0, 2 * A - 1>([&](auto t) { dma(dma_v_slot<decltype(t)::value % R>(), t, T(), blk_of(t)); });
+    dma_barrier<0>();
+    qk(dma_k_slot<0>(), w.s[0]);
+    dma_barrier<0>();
 
-      // Iteration j (J = j mod R is the ring slot of tile j; tile j's scores
-      // live in s[j mod 2]).  Pair p = iterations 2p, 2p+1 reads K(2p+1),
-      // K(2p+2), V(2p-1), V(2p).  Its even iteration loads the operands of
-      // pair p+A: K(j+1+2A), K(j+2+2A), V(j-1+2A), V(j+2A), into the slots
-      // last read in pair p-1; its odd iteration ends with a barrier once
-      // the loads issued A-1 pairs earlier have landed, so a load has A
-      // pairs of iterations to land and only every second iteration waits
-      // at a barrier.  Loads of tiles past the last one load zeros.  QK(j+1)
-      // runs in every iteration, also the last, whose product of a stale
-      // slot is never used: one body throughout keeps the MFMA accumulators
-      // in place.
-      auto iterate = [&](auto j_tag, auto mask_tag, auto first_tag, int j) {
-        constexpr int J = decltype(j_tag)::value;
-        constexpr bool kMask = decltype(mask_tag)::value;
-        constexpr bool kFirst = decltype(first_tag)::value;
-        constexpr int PAR = J & 1;
-        f32x16 &sc = w.s[PAR];
-        f32x16 &sn = w.s[PAR ^ 1];
-        if constexpr (kMask) apply_mask(sc, lim_of(j));
-        if constexpr (kFirst) {
-          const float tm = tile_max(sc, sl2);
-          w.m_run = tm > -INFINITY ? tm : 0.f;
-        }
-        const float mneg = -w.m_run;
-        const unsigned char *ks = dma_k_slot<(J + 1) % R>();
-        const unsigned char *vs = dma_v_slot<(J + R - 1) % R>();
-        // The 16 MFMAs of the iteration alternate between QK(j+1) (even
-        // steps, K fragment i / 2) and PV(j-1) (odd steps, V^T block
-        // c = (i / 2) mod 4 of key half t = i / 8), and each step also
-        // computes one probability of tile j: one MFMA and a sixteenth of
-        // the softmax per step, in this order (scheduling barriers keep the
-        // compiler from regrouping them).  Operands are read from LDS three
-        // steps ahead (two measured ~0.5% slower, four no better).
-        auto operand = [&](int i) -> u32x4 {
-          if ((i & 1) == 0) return *reinterpret_cast<const u32x4 *>(ks + k_rd[i >> 1]);
-          const unsigned char *p = vs + v_rd[(i >> 1) & 3] + 16 * (i >> 3) * DmaGeo::kRowBytes;
-          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 8 * DmaGeo::kRowBytes));
-          u32x4 vw;
-          vw[0] = __builtin_bit_cast(u32x2, lo)[0];
-          vw[1] = __builtin_bit_cast(u32x2, lo)[1];
-          vw[2] = __builtin_bit_cast(u32x2, hi)[0];
-          vw[3] = __builtin_bit_cast(u32x2, hi)[1];
-          return vw;
-        };
-        u32x4 op[16];
-        // Probabilities of tile j go to pfb[j mod 2]; PV(j-1) reads the other.
-        u32x4 (&pf)[2] = w.pfb[PAR];
-        const u32x4 (&pfp)[2] = w.pfb[PAR ^ 1];
-        float rsum0 = 0.f, rsum1 = 0.f;   // row sum: even and odd keys of the tile
-        float x_prev = 0.f;
-        constexpr int kAhead = 3;         // LDS operand reads, steps ahead of their MFMA
+    // Iteration j (J = j mod R is the ring slot of tile j; tile j's scores
+    // live in s[j mod 2]).  Pair p = iterations 2p, 2p+1 reads K(2p+1),
+    // K(2p+2), V(2p-1), V(2p).  Its even iteration loads the operands of
+    // pair p+A: K(j+1+2A), K(j+2+2A), V(j-1+2A), V(j+2A), into the slots
+    // last read in pair p-1; its odd iteration ends with a barrier once
+    // the loads issued A-1 pairs earlier have landed, so a load has A
+    // pairs of iterations to land and only every second iteration waits
+    // at a barrier.  Loads of tiles past the last one load zeros.  QK(j+1)
+    // runs in every iteration, also the last, whose product of a stale
+    // slot is never used: one body throughout keeps the MFMA accumulators
+    // in place.
+    auto iterate = [&](auto j_tag, auto mask_tag, auto first_tag, int j) {
+      constexpr int J = decltype(j_tag)::value;
+      constexpr bool kMask = decltype(mask_tag)::value;
+      constexpr bool kFirst = decltype(first_tag)::value;
+      constexpr int PAR = J & 1;
+      f32x16 (&sc)[NB] = w.s[PAR];
+      f32x16 (&sn)[NB] = w.s[PAR ^ 1];
+      if constexpr (kMask) apply_mask(sc, lim_of(j));
+      if constexpr (kFirst) {
+        const float tm = tile_max(sc, sl2);
+        w.m_run = tm > -INFINITY ? tm : 0.f;
+      }
+      const float mneg = -w.m_run;
+      const unsigned char *ks = dma_k_slot<(J + 1) % R>();
+      const unsigned char *vs = dma_v_slot<(J + R - 1) % R>();
+      // The 16 MFMAs of the iteration alternate between QK(j+1) (even
+      // steps; block b varies fastest, so no two successive ones depend on
+      // each other at head_dim 64) and PV(j-1) (odd steps, V^T block c of
+      // 16-key group t), and each step also computes a sixteenth of tile j's
+      // softmax (one probability at head_dim 128, two at 64), in this order
+      // (scheduling barriers keep the compiler from regrouping them).
+      // Operands are read from LDS three steps ahead (two measured ~0.5%
+      // slower, four no better).
+      constexpr int NC = D / 32;
+      auto operand = [&](int i) -> u32x4 {
+        const int h = i >> 1;
+        if ((i & 1) == 0)
+          return *reinterpret_cast<const u32x4 *>(ks + k_rd[h / NB] + 32 * (h % NB) * G_::kRowBytes);
+        return v_operand(vs, h / NC, h % NC);
+      };
+      u32x4 op[16];
+      // Probabilities of tile j go to pfb[j mod 2]; PV(j-1) reads the other.
+      u32x4 (&pf)[2 * NB] = w.pfb[PAR];
+      const u32x4 (&pfp)[2 * NB] = w.pfb[PAR ^ 1];
+      float rsum0 = 0.f, rsum1 = 0.f;   // row sum: even and odd keys of the tile
+      float x_prev = 0.f;
+      constexpr int kAhead = 3;         // LDS operand reads, steps ahead of their MFMA
 #pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-          if (!kFirst || (i & 1) == 0) op[i] = operand(i);
-          else op[i] = u32x4{0u, 0u, 0u, 0u};
-        }
-        __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < kAhead; ++i) {
+        if (!kFirst || (i & 1) == 0) op[i] = operand(i);
+        else op[i] = u32x4{0u, 0u, 0u, 0u};
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          if (i + kAhead < 16) {
-            if (!kFirst || ((i + kAhead) & 1) == 0) op[i + kAhead] = operand(i + kAhead);
-          }
-          if ((i & 1) == 0) {
-            sn = Elem<DT>::mfma(op[i], w.qf[i >> 1], i == 0 ? f32x16{} : sn);
-          } else if constexpr (!kFirst) {
-            w.oacc[(i >> 1) & 3] = Elem<DT>::mfma(op[i], pfp[i >> 3], w.oacc[(i >> 1) & 3]);
-          }
-          const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i], sl2, mneg));
+      for (int i = 0; i < 16; ++i) {
+        if (i + kAhead < 16) {
+          if (!kFirst || ((i + kAhead) & 1) == 0) op[i + kAhead] = operand(i + kAhead);
+        }
+        const int h = i >> 1;
+        if ((i & 1) == 0) {
+          sn[h % NB] = Elem<DT>::mfma(op[i], w.qf[h / NB], h < NB ? f32x16{} : sn[h % NB]);
+        } else if constexpr (!kFirst) {
+          w.oacc[h % NC] = Elem<DT>::mfma(op[i], pfp[h / NC], w.oacc[h % NC]);
+        }
+        if constexpr (NB == 1) {
+          const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][i], sl2, mneg));
           if (i & 1) {
-            const uint32_t pk = Elem<DT>::pack(x_prev, x);
-            pf[i >> 3][(i & 7) >> 1] = pk;
+            pf[i >> 3][(i & 7) >> 1] = Elem<DT>::pack(x_prev, x);
             rsum0 += x_prev;
             rsum1 += x;
           }
           x_prev = x;
-          if constexpr (PAR == 0) {
-            if (i == 1) dma(dma_k_slot<(J + 1 + 2 * A) % R>(), j + 1 + 2 * A, F(), bk0);
-            if (i == 3) dma(dma_k_slot<(J + 2 + 2 * A) % R>(), j + 2 + 2 * A, F(), bk1);
-            if (i == 5) dma(dma_v_slot<(J - 1 + 2 * A) % R>(), j - 1 + 2 * A, T(), bv0);
-            if (i == 7) dma(dma_v_slot<(J + 2 * A) % R>(), j + 2 * A, T(), bv1);
-            if (i == 9) bn0 = blk_of(j + 3 + 2 * A);
-            if (i == 11) bn1 = blk_of(j + 4 + 2 * A);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        float rs = rsum0 + rsum1;
-        if (!kFirst && __builtin_amdgcn_ballot_w64(!(rs <= Elem<DT>::kSumLimit))) rs = settle_max<D, DT>(w, sc, pf, sl2);
-        w.l_run += rs;
-        if constexpr (PAR == 1) {
-          dma_barrier<4 * (A - 1)>();
-          bv0 = bk0;
-          bv1 = bk1;
-          bk0 = bn0;
-          bk1 = bn1;
-        }
-      };
-      // j = 0 .. R-1 masked (exact for any tile; j = 0 sets the reference
-      // max), then whole rounds of R unmasked tiles, then the rest masked.
-      iterate(std::integral_constant<int, 0>(), T(), T(), 0);
-      static_for<1, R>([&](auto J) {
-        if (decltype(J)::value < n) iterate(J, T(), F(), decltype(J)::value);
-      });
-      int j = R;
-      const int jm = min(j_mask, n);
-      for (; j + R - 1 < jm; j += R) static_for<0, R>([&](auto J) { iterate(J, F(), F(), j + decltype(J)::value); });
-      for (; j < n; j += R)
-        static_for<0, R>([&](auto J) {
-          if (j + decltype(J)::value < n) iterate(J, T(), F(), j + decltype(J)::value);
-        });
-      // PV of the last tile; its V landed before the last pair's barrier.
-      const int last = (n - 1) % R;
-      static_for<0, R>([&](auto S) {
-        constexpr int kS = decltype(S)::value;
-        if (last == kS) pv(dma_v_slot<kS>(), w.pfb[kS & 1]);   // R is even: kS has the parity of n-1
-      });
-      // Loads of tiles past the end may still be in flight.
-      dma_wait_all();
-    }
-  } else {
-    // Staging: chunk c = tid + 512 i of a (K tile, V tile) pair; whether it is
-    // a K or a V chunk is uniform over a wave.
-    int voff[NCH], lds_off[NCH], crow[NCH], ccol[NCH];
-    bool is_v[NCH];
-  #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      is_v[i] = wave * 64 + kThreads * i >= G_::kTileChunks;
-      const int c = tid + kThreads * i - (is_v[i] ? G_::kTileChunks : 0);
-      const int r = c / G_::kChunksPerRow, cc = c % G_::kChunksPerRow;
-      voff[i] = (int)((r * kv_stride + cc * 8) * 2);
-      lds_off[i] = is_v[i] ? G_::kSlots * G_::kTileK + r * G_::kLdsV + cc * 8 : r * G_::kLdsK + cc * 8;
-      crow[i] = r;
-      ccol[i] = wi.kvh * D + cc * 8;
-    }
-    // Regular-cache item: key k of the sequence is row k mod B of local block
-    // rc_ids[rc_off + k / B], read in place.  A wave's chunk i covers 4 (D=128)
-    // or 8 (D=64) consecutive rows of a tile that start on a multiple of that
-    // count, and B >= 16 is a power of two, so those rows share one block: its
-    // index is wave-uniform and the load goes through a buffer resource over
-    // that block's layer slice.  The index of tile t + 1 is read while tile t
-    // is loaded (tiles of one chunk are loaded in order, one per call), so the
-    // data loads never wait on it.  Rows past the range read the clamped last
-    // block; they are masked.
-    const int32_t *rc_ids = kPaged ? a.rc_ids + sd.rc_off : nullptr;
-    const uint16_t *rc_layer = kPaged ? a.rc_base + a.rc_layer_elems : nullptr;
-    const int rc_mask = (1 << a.block_shift) - 1;
-    const uint32_t rc_slice_bytes = (uint32_t)(a.rc_half_elems * 4);
-    int rc_next[NCH];
-  #pragma unroll
-    for (int i = 0; i < NCH; ++i) rc_next[i] = 0;
-    // The index table is read through the constant address space: the host
-    // writes it before the launch and nothing writes it during the kernel, so
-    // the uniform index loads are scalar loads.
-    const __attribute__((address_space(4))) int32_t *rc_ids_c =
-        (const __attribute__((address_space(4))) int32_t *)rc_ids;
-    auto rc_block = [&](int t, int i) {
-      const int row0 = __builtin_amdgcn_readfirstlane(crow[i]);
-      return rc_ids_c[min(k_begin + t * KT + row0, k_end - 1) >> a.block_shift];
-    };
-    // A negative tile index (prologue only) skips that half of the pair.
-    u32x4 lr[NCH];
-    auto stage_load = [&](u32x4 (&lr)[NCH], int kj, int vj) {
-  #pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        const int t = is_v[i] ? vj : kj;
-        if (t < 0) continue;
-        if (kPaged) {
-          const int blk = __builtin_amdgcn_readfirstlane(t == 0 ? rc_block(0, i) : rc_next[i]);
-          rc_next[i] = rc_block(t + 1, i);
-          const uint16_t *base = rc_layer + (int64_t)blk * a.rc_block_elems;
-          const int row = (k_begin + t * KT + crow[i]) & rc_mask;
-          const int off = (int)((row * kv_stride + ccol[i] + (is_v[i] ? a.rc_half_elems : 0)) * 2);
-          lr[i] = __builtin_bit_cast(
-              u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), (short)0,
-                                                           (int)rc_slice_bytes, 0x00020000),
-                         off, 0, 0));
         } else {
-          lr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc(is_v[i] ? vb : kb, t),
-                                                                                   voff[i], 0, 0));
+          const int r = (2 * i) & 15;
+          const float x0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i >> 3][r], sl2, mneg));
+          const float x1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i >> 3][r + 1], sl2, mneg));
+          pf[i >> 2][i & 3] = Elem<DT>::pack(x0, x1);
+          rsum0 += x0;
+          rsum1 += x1;
         }
+        if constexpr (PAR == 0) {
+          if (i == 1) dma(dma_k_slot<(J + 1 + 2 * A) % R>(), j + 1 + 2 * A, F(), bk0);
+          if (i == 3) dma(dma_k_slot<(J + 2 + 2 * A) % R>(), j + 2 + 2 * A, F(), bk1);
+          if (i == 5) dma(dma_v_slot<(J - 1 + 2 * A) % R>(), j - 1 + 2 * A, T(), bv0);
+          if (i == 7) dma(dma_v_slot<(J + 2 * A) % R>(), j + 2 * A, T(), bv1);
+          if (i == 9) bn0 = blk_of(j + 3 + 2 * A);
+          if (i == 11) bn1 = blk_of(j + 4 + 2 * A);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      float rs = rsum0 + rsum1;
+      if (!kFirst && __builtin_amdgcn_ballot_w64(!(rs <= Elem<DT>::kSumLimit))) rs = settle_max<D, DT>(w, sc, pf, sl2);
+      w.l_run += rs;
+      if constexpr (PAR == 1) {
+        dma_barrier<4 * (A - 1)>();
+        bv0 = bk0;
+        bv1 = bk1;
+        bk0 = bn0;
+        bk1 = bn1;
       }
     };
-    // kt / vt: the tiles the K and V chunks hold (ring slot = tile mod 4); a
-    // negative tile skips that half.
-    auto stage_store = [&](const u32x4 (&lr)[NCH], int kt, int vt) {
-  #pragma unroll
-      for (int i = 0; i < NCH; ++i) {
-        const int t = is_v[i] ? vt : kt;
-        if (t >= 0) {
-          const int slot_off = is_v[i] ? (t & 3) * G_::kTileV : (t & 3) * G_::kTileK;
-          *reinterpret_cast<u32x4 *>(smem + lds_off[i] + slot_off) = lr[i];
-        }
-      }
-    };
-    auto slot_k = [&](int t) { return smem + (t & 3) * G_::kTileK; };
-    auto slot_v = [&](int t) { return smem + G_::kSlots * G_::kTileK + (t & 3) * G_::kTileV; };
-
-    if (n > 0 && !timed_out) {
-      // Prologue: K(0), K(1), K(2) and V(0) into the rings (their loads in
-      // flight together), K(3) and V(1) loaded for iteration 0, then QK(0).
-      {
-        u32x4 lb[NCH], lc[NCH];
-        stage_load(lr, 0, 0);
-        stage_load(lb, 1, -1);
-        stage_load(lc, 2, -1);
-        stage_store(lr, 0, 0);
-        stage_store(lb, 1, -1);
-        stage_store(lc, 2, -1);
-        stage_load(lr, 3, 1);
-      }
-      lds_barrier();
-      qk_tile<D, DT>(slot_k(0), w.qf, w.s[0], lane);
-
-      // Iteration j (tile parity PAR): QK(j+1) and PV(j-1) on the MFMA pipe,
-      // softmax(j) on the VALU, then K(j+3), V(j+1) into the rings and K(j+4),
-      // V(j+2) from memory.  Tile j's scores live in s[PAR].  The rings hold
-      // four tiles, so a workgroup barrier is needed only after even
-      // iterations: the two iterations between barriers read K(j+1), V(j-1)
-      // written at least one barrier earlier and write the two slots read
-      // last before that barrier.
-      auto iterate = [&](auto par_tag, auto mask_tag, auto qk_tag, auto pv_tag, auto first_tag, int j) {
-        constexpr int PAR = decltype(par_tag)::value;
-        constexpr bool kMask = decltype(mask_tag)::value;
-        constexpr bool kQk = decltype(qk_tag)::value;
-        constexpr bool kPv = decltype(pv_tag)::value;
-        constexpr bool kFirst = decltype(first_tag)::value;
-        __builtin_assume(j >= 0);
-        f32x16 &sc = w.s[PAR];
-        u32x4 pf[2];
-        if (kQk) qk_tile<D, DT>(slot_k(j + 1), w.qf, w.s[PAR ^ 1], lane);
-        if (kPv) pv_tile<D, DT>(slot_v(j - 1), w.pf_prev, w.oacc, lane);
-        if (kMask) apply_mask(sc, lim_of(j));
-        if (kFirst) {
-          const float tm = tile_max(sc, sl2);
-          w.m_run = tm > -INFINITY ? tm : 0.f;
-        }
-        float rs = softmax_tile<DT>(sc, pf, sl2, w.m_run);
-        if (!kFirst && __builtin_amdgcn_ballot_w64(!(rs <= Elem<DT>::kSumLimit))) rs = settle_max<D, DT>(w, sc, pf, sl2);
-        w.l_run += rs;
-        stage_store(lr, j + 3, j + 1);
-        stage_load(lr, j + 4, j + 2);
-        if (PAR == 0) lds_barrier();
-        w.pf_prev[0] = pf[0];
-        w.pf_prev[1] = pf[1];
-      };
-      using T = std::true_type;
-      using F = std::false_type;
-      using P0 = std::integral_constant<int, 0>;
-      using P1 = std::integral_constant<int, 1>;
-      // j = 0: masked variant (exact for any tile), exact max.
-      if (n > 1) iterate(P0(), T(), T(), F(), T(), 0); else iterate(P0(), T(), F(), F(), T(), 0);
-      // Steady state j = 1 .. n - 2, unrolled by two so that tile parity is
-      // known at compile time: unmasked tiles, then masked ones.
-      int j = 1;
-      auto steady = [&](auto mask_tag, int j_end) {
-        if (j < j_end && (j & 1) == 0) iterate(P0(), mask_tag, T(), T(), F(), j++);
-        for (; j + 1 < j_end; j += 2) {
-          iterate(P1(), mask_tag, T(), T(), F(), j);
-          iterate(P0(), mask_tag, T(), T(), F(), j + 1);
-        }
-        if (j < j_end) iterate(P1(), mask_tag, T(), T(), F(), j++);
-      };
-      steady(F(), min(j_mask, n - 1));
-      steady(T(), n - 1);
-      // j = n - 1: PV(n-2) and softmax(n-1), then drain PV(n-1) (V(n-1) was
-      // written in iteration n-2; whichever of n-2, n-1 is even ended with a
-      // barrier).
-      if (n >= 2) {
-        if ((n - 1) & 1) iterate(P1(), T(), F(), T(), F(), n - 1); else iterate(P0(), T(), F(), T(), F(), n - 1);
-      }
-      pv_tile<D, DT>(slot_v(n - 1), w.pf_prev, w.oacc, lane);
-    }
-
+    // j = 0 .. R-1 masked (exact for any tile; j = 0 sets the reference
+    // max), then whole rounds of R unmasked tiles, then the rest masked.
+    iterate(std::integral_constant<int, 0>(), T(), T(), 0);
+    static_for<1, R>([&](auto J) {
+      if (decltype(J)::value < n) iterate(J, T(), F(), decltype(J)::value);
+    });
+    int j = R;
+    const int jm = min(j_mask, n);
+    for (; j + R - 1 < jm; j += R) static_for<0, R>([&](auto J) { iterate(J, F(), F(), j + decltype(J)::value); });
+    for (; j < n; j += R)
+      static_for<0, R>([&](auto J) {
+        if (j + decltype(J)::value < n) iterate(J, T(), F(), j + decltype(J)::value);
+      });
+    // PV of the last tile; its V landed before the last pair's barrier.
+    const int last = (n - 1) % R;
+    static_for<0, R>([&](auto S) {
+      constexpr int kS = decltype(S)::value;
+      if (last == kS) pv(dma_v_slot<kS>(), w.pfb[kS & 1]);   // R is even: kS has the parity of n-1
+    });
+    // Loads of tiles past the end may still be in flight.
+    dma_wait_all();
   }
 
   // Done with K/V: every load of it has been consumed (loads past the range
@@ -1097,19 +918,10 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
       __hip_atomic_fetch_add(a.done_counter, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  if constexpr (D == 128) {
-    // K/V slots are the namespace-scope arrays above.
-    if (wi.paged)
-      attn_item<D, DT, true>(a, wi, nullptr);
-    else
-      attn_item<D, DT, false>(a, wi, nullptr);
-  } else {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[Geo<D>::kSmem];
-    if (wi.paged)
-      attn_item<D, DT, true>(a, wi, smem);
-    else
-      attn_item<D, DT, false>(a, wi, smem);
-  }
+  if (wi.paged)
+    attn_item<D, DT, true>(a, wi);
+  else
+    attn_item<D, DT, false>(a, wi);
 }
 
 // One work item per workgroup, then (in a layer stack with deferred

@@ -1,0 +1,74 @@
+"""Attention at the edges of its tiles: key counts around the 32-key blocks
+and the tiles loaded into LDS (32 keys at head_dim 128, 64 at 64), with NaN
+rows before and after K and V so that a read outside the range shows, and
+the longest sequence at head_dim 64."""
+
+import numpy as np
+import pytest
+
+from oracle import attention as oa
+from paper_2606_16135_amd import workloads as W
+
+from _gpu_util import bits_to_f64, compare_attention, require_gpu, to_u16
+
+pytestmark = pytest.mark.gpu
+
+
+def _single(sc, p, n, hq, hkv, d, dtype, seed, noalloc=False):
+    """One call over K/V with 80 NaN rows on both sides; output and lse
+    against the oracle."""
+    import torch
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    q = torch.randn((n, hq, d), generator=g, device="cuda").to(td)
+    kv = torch.full((2, p + n + 160, hkv, d), float("nan"), dtype=td, device="cuda")
+    kv[:, 80:80 + p + n] = torch.randn((2, p + n, hkv, d), generator=g, device="cuda").to(td)
+    k, v = kv[0, 80:80 + p + n], kv[1, 80:80 + p + n]
+    out = torch.full((n, hq, d), float("nan"), dtype=td, device="cuda")
+    lse = torch.full((hq, n), float("nan"), dtype=torch.float32, device="cuda")
+    f = (sc.sc_prefill_attn_noalloc if noalloc else
+         sc.sc_prefill_attn if dtype == "bf16" else sc.sc_prefill_attn_f16)
+    f(q.data_ptr(), k.data_ptr(), v.data_ptr(), p, n, hq, hkv, d, out.data_ptr(), lse=lse.data_ptr(),
+      stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    o_ref, l_ref = oa.attention(bits_to_f64(to_u16(q), dtype), bits_to_f64(to_u16(k), dtype),
+                                bits_to_f64(to_u16(v), dtype), [p], [n])
+    what = f"P={p} N={n} heads {hq}/{hkv} D={d} {dtype}"
+    compare_attention(to_u16(out), o_ref, what, dtype)
+    # The row sums are fp32 sums of unrounded probabilities.
+    assert np.abs(lse.cpu().numpy() - l_ref).max() <= 1e-5 * (1 + np.abs(l_ref).max()), what
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_key_counts_around_tile_edges(d, dtype):
+    sc = require_gpu()
+    for i, keys in enumerate([1, 2, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191, 193, 255, 257, 321, 385]):
+        for n in {1, min(keys, 5), keys}:
+            print(f"[edges] D={d} {dtype} keys={keys} N={n}", flush=True)
+            _single(sc, keys - n, n, 8, 2, d, dtype, 100 * i + n)
+
+
+def test_longest_sequence_head_dim_64():
+    """2 GiB of keys less 256 tokens at 8 KV heads x 64 dims: tiles of 64
+    keys past the last one would start beyond the signed 32-bit offsets."""
+    sc = require_gpu()
+    import torch
+    hq, hkv, d, n = 32, 8, 64, 4096
+    tokens = (1 << 31) // (hkv * d * 2) - 256 - 1
+    p = tokens - n
+    assert sc.sc_attn_plan_query([p], [n], hq, hkv)[1] == [1]
+    q, k, v = W.long_sequence_torch(302, p, n, hq, hkv, d, "cuda")
+    out = torch.full((n, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print(f"[longest] P={p} N={n} heads {hq}/{hkv} D={d}", flush=True)
+    sc.sc_prefill_attn(q.data_ptr(), k.data_ptr(), v.data_ptr(), p, n, hq, hkv, d, out.data_ptr(),
+                       stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    for h in (0, hq - 1):
+        g = h // (hq // hkv)
+        kg, vg = (bits_to_f64(to_u16(t[:, g:g + 1])) for t in (k, v))
+        rows = [(0, i, 0) for i in (0, n - 1)]
+        o_ref, _ = oa.attention_rows(bits_to_f64(to_u16(q[:, h:h + 1])), kg, vg, [p], [n], rows)
+        for r, (_, i, _) in enumerate(rows):
+            compare_attention(to_u16(out)[i, h][None, :], o_ref[r][None, :], f"longest row {i} head {h}")
