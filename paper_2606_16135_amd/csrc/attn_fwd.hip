@@ -379,14 +379,10 @@ __device__ __forceinline__ void store_row(const WaveState<D> &w, float inv, int 
 // cache; the two kinds of item are separate copies of the whole body so that
 // each is register-allocated on its own.
 template <int D, int DT, bool kPaged>
-__device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi) {
+__device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi, const SeqDesc &sd) {
   using G_ = Tile<D>;
   constexpr int NB = G_::kBlocks;
   constexpr int TK = G_::kKeys;      // keys per tile
-  // Scalar loads (see load_const), so the key-range and address arithmetic
-  // built from the record stays in scalar registers.
-  const SeqDesc sd = a.seqs != nullptr ? load_const(a.seqs + wi.seq) : a.seq0;
-
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -405,16 +401,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi)
   const int64_t io_row = (int64_t)(sd.q_off + qpos) * a.n_q_heads + h;
 
   WaveState<D> w;
-  // Q^T fragments (B operand): lane holds Q[row][16 k + 8 half .. + 7].
-  {
-    const u32x4 *qp = reinterpret_cast<const u32x4 *>(a.q + io_row * D);
-#pragma unroll
-    for (int k = 0; k < D / 16; ++k) {
-      u32x4 x = {0u, 0u, 0u, 0u};
-      if (valid) x = qp[2 * k + half];
-      w.qf[k] = x;
-    }
-  }
   const float sl2 = a.scale_log2;   // scale * log2(e)
 #pragma unroll
   for (int c = 0; c < D / 32; ++c)
@@ -602,11 +588,29 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi)
     int bv0 = blk_of(2 * A - 1), bv1 = blk_of(2 * A), bk0 = blk_of(2 * A + 1), bk1 = blk_of(2 * A + 2);
     int bn0 = 0, bn1 = 0;
     // Prologue: K(0 .. 2A) and V(0 .. 2A-2), the operands of the first A
-    // pairs; then QK(0).  The first pair loads into the slot QK(0) reads:
-    // a second barrier.
-    static_for<0, 2 * A + 1>([&](auto t) { dma(dma_k_slot<decltype(t)::value % R>(), t, F(), blk_of(t)); });
+    // pairs, and this wave's Q; then QK(0) once K(0) and Q have landed.  The
+    // first pair loads into the slot QK(0) reads: a second barrier.  K(0) is
+    // the first load issued, before anything that waits for memory, so that
+    // its latency and Q's pass together.
+    dma(dma_k_slot<0>(), 0, F(), blk_of(0));
+    __builtin_amdgcn_sched_barrier(0);
+    // Q^T fragments (B operand): lane holds Q[row][16 k + 8 half .. + 7].
+    // The buffer resource covers the item's query rows; rows of the
+    // workgroup past them get an offset outside it and read zeros without a
+    // branch (a masked load made every later load wait for Q).
+    {
+      const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<uint16_t *>(a.q + (int64_t)(sd.q_off + wi.q0) * a.n_q_heads * D), (short)0,
+          wi.nq * a.n_q_heads * (2 * D), 0x00020000);
+      const int qo = valid ? ((qi * a.n_q_heads + h) * D + 8 * half) * 2 : (int)0x80000000u;
+#pragma unroll
+      for (int k = 0; k < D / 16; ++k)
+        w.qf[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(qr, qo + 32 * k, 0, 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<1, 2 * A + 1>([&](auto t) { dma(dma_k_slot<decltype(t)::value % R>(), t, F(), blk_of(t)); });
     static_for<0, 2 * A - 1>([&](auto t) { dma(dma_v_slot<decltype(t)::value % R>(), t, T(), blk_of(t)); });
-    dma_barrier<0>();
+    dma_barrier<4 * A - 1>();
     qk(dma_k_slot<0>(), w.s[0]);
     dma_barrier<0>();
 
@@ -784,7 +788,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs &a, const int64_t (&ro
 #pragma unroll
   for (int i = 0; i < NR; ++i) {
     const int64_t row = rows_i[i] < 0 ? 0 : rows_i[i];
-    const int token = (int)(row / a.n_q_heads);
+    const int token = (int)((uint32_t)row / (uint32_t)a.n_q_heads);
     int lo = 0;
     if (a.n_seqs > 1) {
       int hi = a.n_seqs - 1;
@@ -809,8 +813,8 @@ __device__ __forceinline__ void merge_rows(const AttnArgs &a, const int64_t (&ro
     const int S = rows_i[i] < 0 ? 0 : sd[i].n_splits;
     if (S <= 1) continue;
     const int64_t row = rows_i[i];
-    const int token = (int)(row / a.n_q_heads);
-    const int h = (int)(row - (int64_t)token * a.n_q_heads);
+    const int token = (int)((uint32_t)row / (uint32_t)a.n_q_heads);
+    const int h = (int)((uint32_t)row - (uint32_t)token * (uint32_t)a.n_q_heads);
     const int64_t io_row = (int64_t)(sd[i].q_off + token - sd[i].cu_q) * a.n_q_heads + h;
     float mx = -INFINITY;
 #pragma unroll
@@ -910,7 +914,12 @@ __device__ __forceinline__ WorkItem implicit_item(const AttnArgs &a, int w) {
 
 template <int D, int DT>
 __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
-  const WorkItem wi = a.items != nullptr ? load_const(a.items + blockIdx.x) : implicit_item(a, blockIdx.x);
+  AttnItem it;
+  if (a.items != nullptr)
+    it = load_const(a.items + blockIdx.x);
+  else
+    it = AttnItem{implicit_item(a, blockIdx.x), a.seq0};
+  const WorkItem &wi = it.wi;
   if (wi.seq < 0) {
     // Padding slot (XCD placement): no K/V to read, but it counts as done
     // like every other workgroup of the launch.
@@ -919,9 +928,9 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
     return;
   }
   if (wi.paged)
-    attn_item<D, DT, true>(a, wi);
+    attn_item<D, DT, true>(a, wi, it.sd);
   else
-    attn_item<D, DT, false>(a, wi);
+    attn_item<D, DT, false>(a, wi, it.sd);
 }
 
 // One work item per workgroup, then (in a layer stack with deferred

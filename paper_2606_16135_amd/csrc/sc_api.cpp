@@ -405,10 +405,12 @@ sc_status get_workspace(int device, hipStream_t stream, size_t bytes, void **out
 
 sc_status upload_plan(AttnPlan *plan) {
   if (plan->n_items == 0) return SC_OK;
-  SC_HIP(hipMalloc(&plan->d_items, plan->items.size() * sizeof(WorkItem)));
+  std::vector<AttnItem> items(plan->items.size());
+  for (size_t i = 0; i < items.size(); ++i)
+    items[i] = AttnItem{plan->items[i], plan->items[i].seq >= 0 ? plan->seqs[plan->items[i].seq] : SeqDesc{}};
+  SC_HIP(hipMalloc(&plan->d_items, items.size() * sizeof(AttnItem)));
   SC_HIP(hipMalloc(&plan->d_seqs, plan->seqs.size() * sizeof(SeqDesc)));
-  SC_HIP(hipMemcpy(plan->d_items, plan->items.data(), plan->items.size() * sizeof(WorkItem),
-                   hipMemcpyHostToDevice));
+  SC_HIP(hipMemcpy(plan->d_items, items.data(), items.size() * sizeof(AttnItem), hipMemcpyHostToDevice));
   SC_HIP(hipMemcpy(plan->d_seqs, plan->seqs.data(), plan->seqs.size() * sizeof(SeqDesc),
                    hipMemcpyHostToDevice));
   return SC_OK;
@@ -512,8 +514,9 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
   a.out = static_cast<uint16_t *>(out);
   a.lse = lse;
   a.items = plan.d_items;
-  a.seqs = plan.d_seqs;
   a.n_seqs = (int32_t)plan.seqs.size();
+  a.seqs = a.n_seqs > 1 ? plan.d_seqs : nullptr;
+  a.seq0 = plan.seqs[0];
   a.total_q = (int32_t)plan.total_q;
   a.n_q_heads = hq;
   a.n_kv_heads = hkv;
@@ -582,8 +585,9 @@ sc_status run_merge(const AttnPlan &plan, const void *ws, void *out, int hq, int
   plan_ws_bytes(plan, hq, head_dim, &lse_off);
   AttnArgs a{};
   a.out = static_cast<uint16_t *>(out);
-  a.seqs = plan.d_seqs;
   a.n_seqs = (int32_t)plan.seqs.size();
+  a.seqs = a.n_seqs > 1 ? plan.d_seqs : nullptr;
+  a.seq0 = plan.seqs[0];
   a.total_q = (int32_t)plan.total_q;
   a.n_q_heads = hq;
   a.n_kv_heads = hkv;

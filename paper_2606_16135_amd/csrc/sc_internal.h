@@ -120,14 +120,24 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 32, "WorkItem layout");
 
+// What a workgroup reads before anything else: its item and a copy of the
+// item's sequence record, one 64-byte scalar load (fetching the sequence by
+// the item's index was a second memory round trip in front of the first K
+// load).
+struct AttnItem {
+  WorkItem wi;
+  SeqDesc sd;
+};
+static_assert(sizeof(AttnItem) == 64, "AttnItem layout");
+
 struct AttnArgs {
   const uint16_t *q;
   const uint16_t *k;
   const uint16_t *v;
   uint16_t *out;
   float *lse;             // nullable, [Hq][total_q]
-  const WorkItem *items;
-  const SeqDesc *seqs;
+  const AttnItem *items;
+  const SeqDesc *seqs;    // for the merge of several sequences; nullptr: one sequence, seq0
   uint16_t *part_o;       // [max_splits][total_q][Hq][D] normalised partial outputs, element type
   float *part_lse;        // [max_splits][total_q][Hq]
   int32_t n_seqs;
@@ -168,7 +178,7 @@ struct AttnArgs {
   int32_t block_shift;
   // Implicit work list (one sequence, no regular cache; the allocation-free
   // entry point): items == nullptr and seqs == nullptr.  The sequence is
-  // seq0; workgroup w takes item g = (w % 8) * imp_per_xcd + w / 8 of the
+  // seq0 (also set by plans of one sequence, for the merge); workgroup w takes item g = (w % 8) * imp_per_xcd + w / 8 of the
   // list ordered (KV head, query tile, key split), so consecutive items --
   // one KV head's -- share an XCD.  Split sp of a tile with `keys` keys
   // covers tiles [sp * t / S, (sp + 1) * t / S) of its t = ceil(keys / 32)
@@ -228,7 +238,7 @@ struct AttnPlan {
   int n_real_items = 0;
   std::vector<WorkItem> items;
   std::vector<SeqDesc> seqs;
-  WorkItem *d_items = nullptr;
+  AttnItem *d_items = nullptr;
   SeqDesc *d_seqs = nullptr;
   int64_t total_q = 0;
 };
