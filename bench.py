@@ -55,11 +55,11 @@ ROTATE_BYTES = 512 << 20         # destination buffers the standalone fetch cycl
 # with the hash of the attention source's code (comments left out) they were
 # taken on; a stale entry (the code changed since) is reported as null.
 PMC_TRAFFIC = {
-    "llama3-8b-P8192-N512": (80481765, "4ba710f1265470eb"),
-    "llama3-8b-batch16-varlen": (705816836, "4ba710f1265470eb"),
-    "qwen-14b-P32768-N1024": (364153977, "4ba710f1265470eb"),
-    "llama3-8b-P131072-N2048-hosttier": (1191660843, "4ba710f1265470eb"),
-    "llama3-8b-P8192-N512-rc0.5": (79959614, "4ba710f1265470eb"),
+    "llama3-8b-P8192-N512": (80632450, "fa3230158194cb02"),
+    "llama3-8b-batch16-varlen": (706166482, "fa3230158194cb02"),
+    "qwen-14b-P32768-N1024": (364113511, "fa3230158194cb02"),
+    "llama3-8b-P131072-N2048-hosttier": (1190678981, "fa3230158194cb02"),
+    "llama3-8b-P8192-N512-rc0.5": (79954541, "fa3230158194cb02"),
 }
 
 

@@ -777,7 +777,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
 // Every split's lse and partial chunk of all NR rows are loaded before any
 // is used: one memory round trip, whatever the split count (merging a few
 // thousand rows is latency-bound, not bandwidth-bound).
-template <int D, int DT, int NR, int SMAX = kAttnMaxSplits>
+template <int D, int DT, int NR, int SMAX>
 __device__ __forceinline__ void merge_rows(const AttnArgs &a, const int64_t (&rows_i)[NR], int sub,
                                            const uint16_t *part_o, const float *part_lse, uint16_t *out,
                                            float *lse_out) {
@@ -880,6 +880,8 @@ template <int D, int DT>
 __device__ __forceinline__ void deferred_merge(const AttnArgs &a) {
   if (a.dm_max_splits <= 4)
     deferred_merge_n<D, DT, 4, 4>(a);
+  else if (a.dm_max_splits <= 16)
+    deferred_merge_n<D, DT, 1, 16>(a);
   else
     deferred_merge_n<D, DT, 1, kAttnMaxSplits>(a);
 }
@@ -941,7 +943,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnArgs a) {
   if (a.dm_out != nullptr) deferred_merge<D, DT>(a);
 }
 
-template <int D, int DT>
+template <int D, int DT, int SMAX>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   constexpr int LPR = D / 8;
   constexpr int RPB = 256 / LPR;
@@ -949,7 +951,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int64_t row = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR;
   if (row >= rows) return;
   const int64_t rr[1] = {row};
-  merge_rows<D, DT, 1>(a, rr, threadIdx.x % LPR, a.part_o, a.part_lse, a.out, a.lse);
+  merge_rows<D, DT, 1, SMAX>(a, rr, threadIdx.x % LPR, a.part_o, a.part_lse, a.out, a.lse);
 }
 
 // Split-key partials of the allocation-free entry point: one array per
@@ -1031,20 +1033,24 @@ size_t attn_fwd_lds_bytes(int head_dim) {
   return m;
 }
 
-hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, hipStream_t stream) {
+hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, int max_splits, hipStream_t stream) {
   const int64_t rows = (int64_t)a.total_q * a.n_q_heads;
   if (rows <= 0) return hipSuccess;
   const dim3 grid((unsigned)((rows * (head_dim / 8) + 255) / 256)), block(256);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, a); };
+  // Two bounds on the splits of a row: the registers of the wider one would
+  // halve the waves in flight of calls with many rows, which have few splits.
+  const bool wide = max_splits > 16;
   if (head_dim == 128) {
     if (a.dtype == SC_DTYPE_F16)
-      hipLaunchKernelGGL((attn_merge_kernel<128, SC_DTYPE_F16>), grid, block, 0, stream, a);
+      wide ? launch(attn_merge_kernel<128, SC_DTYPE_F16, kAttnMaxSplits>) : launch(attn_merge_kernel<128, SC_DTYPE_F16, 16>);
     else
-      hipLaunchKernelGGL((attn_merge_kernel<128, SC_DTYPE_BF16>), grid, block, 0, stream, a);
+      wide ? launch(attn_merge_kernel<128, SC_DTYPE_BF16, kAttnMaxSplits>) : launch(attn_merge_kernel<128, SC_DTYPE_BF16, 16>);
   } else {
     if (a.dtype == SC_DTYPE_F16)
-      hipLaunchKernelGGL((attn_merge_kernel<64, SC_DTYPE_F16>), grid, block, 0, stream, a);
+      wide ? launch(attn_merge_kernel<64, SC_DTYPE_F16, kAttnMaxSplits>) : launch(attn_merge_kernel<64, SC_DTYPE_F16, 16>);
     else
-      hipLaunchKernelGGL((attn_merge_kernel<64, SC_DTYPE_BF16>), grid, block, 0, stream, a);
+      wide ? launch(attn_merge_kernel<64, SC_DTYPE_BF16, kAttnMaxSplits>) : launch(attn_merge_kernel<64, SC_DTYPE_BF16, 16>);
   }
   return hipGetLastError();
 }

@@ -61,6 +61,15 @@ namespace {
 constexpr int kXcds = 8;                 // MI355X: workgroup w is dispatched to XCD w % 8
 constexpr int kMinSplitKeys = 2 * kAttnKeyTile;   // the schedule model below picks among the rest
 constexpr int kMaxSplits = kAttnMaxSplits;
+// More splits than this only where they still run in one round of
+// workgroups, i.e. for the fewest query tiles: a turn of at most 256 / group
+// tokens has one per KV head, and with 8 KV heads 16 splits leave half of
+// the CUs idle.  fp16 call of 40/8 heads, P=32768, N=48: 57.0 us with 16
+// splits, 46.2 with the 32 chosen now; P=32768, N=8 of 32/8 heads 51 -> 39,
+// P=8192, N=1 18.8 -> 15.9, P=4096, N=16 unchanged (14.7).  With more tiles
+// the extra partials only add rounds and merge traffic (P=3000, N=100:
+// 11 splits 21 us, 20 splits 60).
+constexpr int kManySplits = 16;
 constexpr int kResidentPerCu = 1;        // one 8-wave workgroup per CU (LDS ring, 2 waves per SIMD)
 constexpr int kQueryDefaultSlots = 256 * kResidentPerCu;   // MI355X: 256 CUs
 constexpr int64_t kItemOverheadKeys = 128;  // prologue + epilogue, in keys
@@ -89,6 +98,7 @@ struct TileDesc {
 
 // Longest-processing-time schedule of `costs` on `slots` identical slots.
 int64_t lpt_makespan(std::vector<int64_t> &costs, int slots) {
+  if (!costs.empty() && costs.size() <= (size_t)std::max(1, slots)) return *std::max_element(costs.begin(), costs.end());
   std::sort(costs.begin(), costs.end(), std::greater<int64_t>());
   std::vector<int64_t> heap(std::max(1, slots), 0);   // min-heap of slot loads
   auto cmp = std::greater<int64_t>();
@@ -126,6 +136,7 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
     int64_t chunk = (max_kv + s - 1) / s;
     chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
     if (s > 1 && chunk < kMinSplitKeys) break;
+    if (s > kManySplits && (int64_t)n_qt * hkv * s > slots) break;
     const int S = splits_of(chunk);
     if ((int64_t)n_qt * S > kNoAllocMaxCosts) return false;
     int nc = 0;
@@ -139,17 +150,20 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
         costs[nc++] = (std::max(b0, b1) - b0) + kItemOverheadKeys + (S > 1 ? kMergeOverheadKeys : 0);
       }
     }
-    std::sort(costs, costs + nc, std::greater<int64_t>());
-    std::fill(heap, heap + slots, (int64_t)0);   // all zero: already a heap
-    auto cmp = std::greater<int64_t>();
-    for (int i = 0; i < nc; ++i)
-      for (int g = 0; g < hkv; ++g) {
-        std::pop_heap(heap, heap + slots, cmp);
-        heap[slots - 1] += costs[i];
-        std::push_heap(heap, heap + slots, cmp);
-      }
-    const int64_t makespan = *std::max_element(heap, heap + slots);
     const int64_t n = (int64_t)nc * hkv;
+    int64_t makespan = *std::max_element(costs, costs + nc);   // one round of workgroups
+    if (n > slots) {
+      std::sort(costs, costs + nc, std::greater<int64_t>());
+      std::fill(heap, heap + slots, (int64_t)0);   // all zero: already a heap
+      auto cmp = std::greater<int64_t>();
+      for (int i = 0; i < nc; ++i)
+        for (int g = 0; g < hkv; ++g) {
+          std::pop_heap(heap, heap + slots, cmp);
+          heap[slots - 1] += costs[i];
+          std::push_heap(heap, heap + slots, cmp);
+        }
+      makespan = *std::max_element(heap, heap + slots);
+    }
     const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
     const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
     const int64_t span = makespan + merge + kItemSharedKeys * n;
@@ -295,6 +309,7 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
     int64_t chunk = (max_kv + s - 1) / s;
     chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
     if (s > 1 && chunk < kMinSplitKeys) break;
+    if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
     std::vector<int64_t> costs;
     std::vector<Range> rs;
     for (const TileDesc &t : tiles) {
@@ -570,7 +585,7 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
   if (e != hipSuccess) return fail_hip(e, "attn_fwd launch");
   if (after_fwd) SC_HIP(hipEventRecord(after_fwd, stream));
   if (plan.max_splits > 1 && !sm) {
-    e = launch_attn_merge(a, head_dim, stream);
+    e = launch_attn_merge(a, head_dim, plan.max_splits, stream);
     if (e != hipSuccess) return fail_hip(e, "attn_merge launch");
   }
   return SC_OK;
@@ -596,7 +611,7 @@ sc_status run_merge(const AttnPlan &plan, const void *ws, void *out, int hq, int
   a.dtype = dtype;
   a.part_o = static_cast<uint16_t *>(const_cast<void *>(ws));
   a.part_lse = reinterpret_cast<float *>(static_cast<char *>(const_cast<void *>(ws)) + lse_off);
-  hipError_t e = launch_attn_merge(a, head_dim, stream);
+  hipError_t e = launch_attn_merge(a, head_dim, plan.max_splits, stream);
   return e == hipSuccess ? SC_OK : fail_hip(e, "attn_merge launch");
 }
 
@@ -1626,7 +1641,7 @@ sc_status sc_prefill_attn_noalloc(const void *q, const void *k_active, const voi
   hipError_t e = launch_attn_fwd(a, head_dim, kXcds * a.imp_per_xcd, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(e, "attn_fwd launch");
   if (S > 1) {
-    e = launch_attn_merge(a, head_dim, (hipStream_t)stream);
+    e = launch_attn_merge(a, head_dim, S, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "attn_merge launch");
   }
   return SC_OK;

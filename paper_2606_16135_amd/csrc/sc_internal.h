@@ -213,7 +213,7 @@ inline bool keys_fit_offsets(int64_t tokens, int n_kv_heads, int head_dim) {
   const int64_t row_bytes = (int64_t)n_kv_heads * head_dim * 2;   // head_dim is 64 or 128
   return row_bytes > 0 && tokens >= 0 && tokens + kKeyOffsetMarginTokens <= (((int64_t)1 << 31) - 1) / row_bytes;
 }
-constexpr int kAttnMaxSplits = 16; // key splits per sequence (merge kernel bound)
+constexpr int kAttnMaxSplits = 32; // key splits per sequence (merge kernel bound)
 // Polls of the ready flag before an attention workgroup gives up (about a
 // second), and the limit a forced time-out uses.
 constexpr int kAttnReadySpinLimit = 1 << 22;
@@ -227,7 +227,7 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes);
 size_t attn_fwd_lds_bytes(int head_dim);
 int attn_fwd_vgprs(int head_dim);   // per work item, -1 if unknown
 int kv_copy_vgprs();                // largest of the three copy kernels
-hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, hipStream_t stream);
+hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, int max_splits, hipStream_t stream);
 
 struct AttnPlan {
   bool paged = false;              // some items read the regular cache in place

@@ -72,3 +72,49 @@ def test_longest_sequence_head_dim_64():
         o_ref, _ = oa.attention_rows(bits_to_f64(to_u16(q[:, h:h + 1])), kg, vg, [p], [n], rows)
         for r, (_, i, _) in enumerate(rows):
             compare_attention(to_u16(out)[i, h][None, :], o_ref[r][None, :], f"longest row {i} head {h}")
+
+
+# One query tile per KV head and more than 16 key splits: (P, N, Hq, Hkv).
+MANY_SPLITS = [(4100, 3, 16, 4), (6000, 60, 8, 4), (9001, 17, 40, 8)]
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (64, "f16"), (128, "bf16"), (128, "f16")])
+def test_more_than_16_splits(d, dtype):
+    sc = require_gpu()
+    for i, (p, n, hq, hkv) in enumerate(MANY_SPLITS):
+        splits = sc.sc_attn_plan_query([p], [n], hq, hkv)[1][0]
+        assert 16 < splits <= 32 and splits * hkv <= 256, (p, n, splits)
+        for noalloc in ([False, True] if dtype == "bf16" else [False]):
+            print(f"[splits] D={d} {dtype} P={p} N={n} splits={splits} noalloc={noalloc}", flush=True)
+            _single(sc, p, n, hq, hkv, d, dtype, 7000 + i, noalloc)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_more_than_16_splits_in_a_stack(d):
+    """Merges deferred to the next layer's kernel and the last layer's own."""
+    sc = require_gpu()
+    import torch
+    from oracle import kvcache as ok
+    from _gpu_util import DevicePool, from_u16, new_active
+    L, hq, hkv = 3, 16, 4
+    wl = W.small_workload(7100, [5000], [21], L, hq, hkv, d)
+    assert sc.sc_attn_plan_query([5000], [21], hq, hkv)[1][0] > 16
+    pool = W.pool_numpy(wl)
+    dp = DevicePool(sc, wl, pool)
+    try:
+        ins = [W.layer_inputs_numpy(wl, l) for l in range(L)]
+        dev = [[from_u16(x, "cuda", wl.dtype) for x in t] for t in ins]
+        outs = [torch.full((wl.total_q, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(L)]
+        slots = [new_active(sc, wl) for _ in range(2)]
+        copy = torch.cuda.Stream()
+        sc.sc_prefill_stack(dp.handle, dp.table, *([x[i].data_ptr() for x in dev] for i in range(3)),
+                            [o.data_ptr() for o in outs], [s[2] for s in slots], hq,
+                            compute_stream=torch.cuda.current_stream().cuda_stream, copy_stream=copy.cuda_stream)
+        torch.cuda.synchronize()
+        for l, (q, kn, vn) in enumerate(ins):
+            ka, va = ok.gather_layer(pool, wl.block_ids, wl.cu_blocks, wl.prefix_len, wl.new_len, l)
+            kf, vf = ok.append_new(ka, va, kn, vn, wl.prefix_len, wl.new_len)
+            ref, _ = oa.attention(bits_to_f64(q), bits_to_f64(kf), bits_to_f64(vf), wl.prefix_len, wl.new_len)
+            compare_attention(to_u16(outs[l]), ref, f"layer {l}")
+    finally:
+        dp.close()
