@@ -202,40 +202,20 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 
-// K/V ring slots, loaded straight into LDS (see attn_item).
-// One array per slot and operand, so the compiler can tell that a load in
-// flight into one slot does not alias reads of another and needs no wait.
-// Pairs of iterations a tile load has to land in, and the ring size that
-// allows (tiles read in the A pairs after a load plus the two it loads).
-// One pair is enough: with two or three (96 or 128 KiB of LDS) the kernel
-// measured 1.5-3% slower on the 8B, 14B and long-prefix shapes.
-constexpr int kDmaAhead = 1;
-constexpr int kDmaRing = 2 * kDmaAhead + 2;
-static_assert(kDmaAhead >= 1 && kDmaRing <= 8, "ring of at most 8 slots");
-#define SC_DMA_SLOT(n)                                                          \
-  __shared__ __attribute__((aligned(1024))) unsigned char dma_k##n[Tile<128>::kSlotBytes]; \
-  __shared__ __attribute__((aligned(1024))) unsigned char dma_v##n[Tile<128>::kSlotBytes];
-SC_DMA_SLOT(0)
-SC_DMA_SLOT(1)
-SC_DMA_SLOT(2)
-SC_DMA_SLOT(3)
-SC_DMA_SLOT(4)
-SC_DMA_SLOT(5)
-SC_DMA_SLOT(6)
-SC_DMA_SLOT(7)
-#undef SC_DMA_SLOT
-template <int S>
-__device__ __forceinline__ unsigned char *dma_k_slot() {
-  static_assert(S >= 0 && S < kDmaRing, "ring slot");
-  return S == 0 ? dma_k0 : S == 1 ? dma_k1 : S == 2 ? dma_k2 : S == 3 ? dma_k3
-       : S == 4 ? dma_k4 : S == 5 ? dma_k5 : S == 6 ? dma_k6 : dma_k7;
-}
-template <int S>
-__device__ __forceinline__ unsigned char *dma_v_slot() {
-  static_assert(S >= 0 && S < kDmaRing, "ring slot");
-  return S == 0 ? dma_v0 : S == 1 ? dma_v1 : S == 2 ? dma_v2 : S == 3 ? dma_v3
-       : S == 4 ? dma_v4 : S == 5 ? dma_v5 : S == 6 ? dma_v6 : dma_v7;
-}
+// K/V slots of 8 KiB in the workgroup's `ring`, loaded straight into LDS
+// (see attn_item).  Ordinary items: slot s of the four K slots at 8 s KiB, of
+// the four V slots 32 KiB further.  Narrow items: two stages of four key groups' slots, K at
+// 32 stage + 8 group KiB, V 64 KiB further.  A tile's load has one pair of
+// iterations to land in (one iteration for narrow items); two or three pairs
+// (rings of 6 or 8 slots) measured 1.5-3% slower on the 8B, 14B and
+// long-prefix shapes and 3-15% slower on short turns that stream K/V from
+// HBM once.
+constexpr int kRing = 4;
+constexpr int kNarrowGroups = 4;
+constexpr int kSlot = Tile<128>::kSlotBytes;
+// Narrow items: each wave's reference max and row sums (32 rows), for the
+// waves that combine them.
+__shared__ f32x2 narrow_ml[8][32];
 
 // f(integral_constant<int, i>) for i = B .. E-1, unrolled.
 template <int B, int E, class Fn>
@@ -245,8 +225,6 @@ __device__ __forceinline__ void static_for(Fn &&f) {
     static_for<B + 1, E>(f);
   }
 }
-
-typedef __attribute__((address_space(3))) void lds_void;
 
 // Wait until at most VM vector-memory operations of this wave (loads into
 // LDS included) are in flight and its LDS and scalar loads are done, then a
@@ -260,6 +238,22 @@ __device__ __forceinline__ void dma_barrier() {
   __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4) | (0 << 8));
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+// One wave's 1 KiB load into LDS at byte address `lds` (in M0 for the
+// instruction, which needs one wait state after the write of M0; nothing
+// else in these kernels uses M0, and saving it cost 0.5-1% of a call).
+// Written out because all slots are one array (narrow items pick theirs at
+// run time): around the builtin the compiler would wait for every load in
+// flight before any LDS read.  The waits are dma_barrier's; there is no
+// output register.
+__device__ __forceinline__ void load_to_lds(uint32_t lds, int voff, u32x4 rsrc) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
 }
 
 // Wait for every vector-memory operation of this wave.
@@ -351,35 +345,56 @@ __device__ __forceinline__ float settle_max(WaveState<D> &w, const f32x16 (&s)[T
 // so every lane writes whole 16-byte chunks (the two halves of a row fill
 // 32 contiguous bytes per store).  v_permlane32_swap exchanges lanes 32-63
 // of its first operand with lanes 0-31 of its second.
+template <int DT>
+__device__ __forceinline__ void store_chunk(const float (&x)[8], float inv, uint16_t *dst) {
+  // A: dims 4 half + [0, 4) of 16; B: the same + 8.
+  uint32_t A[2], B[2];
+  A[0] = Elem<DT>::pack(x[0] * inv, x[1] * inv);
+  A[1] = Elem<DT>::pack(x[2] * inv, x[3] * inv);
+  B[0] = Elem<DT>::pack(x[4] * inv, x[5] * inv);
+  B[1] = Elem<DT>::pack(x[6] * inv, x[7] * inv);
+  u32x4 st;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    // Half 0 receives the other half's A, half 1 the other half's B.
+    const auto r = __builtin_amdgcn_permlane32_swap(A[e], B[e], false, false);
+    st[e] = (uint32_t)r[0];
+    st[2 + e] = (uint32_t)r[1];
+  }
+  *reinterpret_cast<u32x4 *>(dst) = st;
+}
+
 template <int D, int DT>
 __device__ __forceinline__ void store_row(const WaveState<D> &w, float inv, int half, uint16_t *dst) {
 #pragma unroll
   for (int c = 0; c < D / 32; ++c)
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-      // A: dims 32c + 16m + 4 half + [0, 4); B: the same + 8.
-      uint32_t A[2], B[2];
-      A[0] = Elem<DT>::pack(w.oacc[c][8 * m + 0] * inv, w.oacc[c][8 * m + 1] * inv);
-      A[1] = Elem<DT>::pack(w.oacc[c][8 * m + 2] * inv, w.oacc[c][8 * m + 3] * inv);
-      B[0] = Elem<DT>::pack(w.oacc[c][8 * m + 4] * inv, w.oacc[c][8 * m + 5] * inv);
-      B[1] = Elem<DT>::pack(w.oacc[c][8 * m + 6] * inv, w.oacc[c][8 * m + 7] * inv);
-      u32x4 st;
+      float x[8];
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        // Half 0 receives the other half's A, half 1 the other half's B.
-        const auto r = __builtin_amdgcn_permlane32_swap(A[e], B[e], false, false);
-        st[e] = (uint32_t)r[0];
-        st[2 + e] = (uint32_t)r[1];
-      }
-      *reinterpret_cast<u32x4 *>(dst + 32 * c + 16 * m + 8 * half) = st;
+      for (int e = 0; e < 8; ++e) x[e] = w.oacc[c][8 * m + e];
+      store_chunk<DT>(x, inv, dst + 32 * c + 16 * m + 8 * half);
     }
 }
 
 // One work item.  kPaged: its keys are read in place from the regular
-// cache; the two kinds of item are separate copies of the whole body so that
-// each is register-allocated on its own.
-template <int D, int DT, bool kPaged>
-__device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi, const SeqDesc &sd) {
+// cache.  KG = 1: the eight waves hold 256 rows.  KG = 4, a narrow item of
+// at most 64 rows: two blocks of 32 rows times four key groups.  Wave w
+// holds rows 32 (w / 4) .. + 31 and takes the tiles kg + 4 j, kg = w mod 4,
+// so that every wave has work, and the groups are combined through LDS at
+// the end.  An iteration stages four K and four V tiles and ends with a
+// barrier once they have landed: 64 KiB in flight per CU.  An ordinary item
+// runs its 256 rows' worth of MFMAs whatever it holds; a narrow one takes a
+// third to a quarter of the time per key, plus 1.7 us (3.4 with two row
+// blocks) for its start and the combination.  Calls of 32/8 heads, ordinary
+// against narrow: P=8192, N=1 15.6 -> 13.8 us, P=32768, N=8 36.3 -> 33.5,
+// P=2048, N=8 11.4 -> 10.1, P=256, N=4 8.5 -> 6.9 (one split, no merge);
+// layer stack of 40/8 heads in chunks of 256 tokens, whose last query tile
+// has 5 rows: 1610 -> 1540 us.  The kinds are separate copies of the whole body so that each is register-allocated on
+// its own.
+template <int D, int DT, bool kPaged, int KG>
+__device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring, const WorkItem &wi, const SeqDesc &sd) {
+  static_assert(KG == 1 || (KG == kNarrowGroups && !kPaged), "kinds of item");
   using G_ = Tile<D>;
   constexpr int NB = G_::kBlocks;
   constexpr int TK = G_::kKeys;      // keys per tile
@@ -389,7 +404,9 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
   const int half = lane >> 5;
   const int col = lane & 31;
   const int group = a.group;
-  const int row = wave * 32 + col;
+  const int kg = KG == 1 ? 0 : wave % KG;          // key group
+  const int rb = KG == 1 ? wave : wave / KG;       // block of 32 rows
+  const int row = rb * 32 + col;
   const int qi = row / group;
   const int hg = row - qi * group;
   const bool valid = qi < wi.nq;
@@ -428,9 +445,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
   // First tile that needs the mask, the same for the whole workgroup: it
   // reaches past the key range or past the diagonal of the first query.
   const int diag0 = sd.prefix + wi.q0;
-  const int j_mask = max(0, min(n, (min(k_end, diag0 + 1) - k_begin) / TK));
+  const int j_mask = max(0, min(n, (min(k_end, diag0 + 1) - k_begin) / TK)) / KG;
+  const int n_it = (n + KG - 1) / KG;   // iterations
   const int my_last = min(k_end - 1, sd.prefix + qpos);
-  auto lim_of = [&](int j) { return my_last - (k_begin + j * TK) - 4 * half; };
+  auto lim_of = [&](int j) { return my_last - (k_begin + (j * KG + kg) * TK) - 4 * half; };
 
   // Device-side dependency on the copy stream (see AttnArgs::ready_flag).
   // The poll is a relaxed device-scope load (no cache invalidation per
@@ -464,33 +482,36 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
 
   // K and V tiles go from memory straight into LDS (buffer loads with the
   // LDS flag; no staging registers).  Wave w loads kRowsPerLoad consecutive
-  // rows of every K and V tile: one 16-byte load per lane and operand, lane
-  // i filling bytes 16 i .. 16 i + 15 of the wave's rows.  Rows are unpadded
+  // rows of every K and V tile (narrow: half of its own group's tile, in
+  // four loads): one 16-byte load per lane, lane i filling bytes 16 i ..
+  // 16 i + 15 of the wave's rows.  Rows are unpadded
   // and swizzled (see Tile), which keeps the K fragment reads and the V
   // transpose reads free of bank conflicts: each lane loads the chunk that
   // belongs at its position.
   const int row_bytes = (int)(kv_stride * 2);
-  const int my_row = G_::kRowsPerLoad * wave;
-  int voff_k, voff_v;
-  {
-    const int r = lane / G_::kChunksPerRow;
+  const int my_row = KG == 1 ? G_::kRowsPerLoad * wave : rb * (TK / 2);
+  int voff_k[KG], voff_v;   // KG loads per tile; V's swizzle repeats with them
+#pragma unroll
+  for (int i = 0; i < KG; ++i) {
+    const int r = i * G_::kRowsPerLoad + lane / G_::kChunksPerRow;
     const int c = lane % G_::kChunksPerRow;
-    voff_k = r * row_bytes + ((c ^ G_::swz_k(my_row + r)) << 4);
-    voff_v = r * row_bytes + ((c ^ G_::swz_v(my_row + r)) << 4);
+    voff_k[i] = r * row_bytes + ((c ^ G_::swz_k(my_row + r)) << 4);
+    if (i == 0) voff_v = r * row_bytes + ((c ^ G_::swz_v(my_row + r)) << 4);
   }
-  // This lane's LDS read offsets within a slot: K fragment k of block 0
-  // (row col, chunk 2 k + half) and the transpose read of dim block c (key
-  // row tr_row; the other blocks and key rows of the product are
-  // immediates, as the swizzles repeat every 16 rows).
+  // This lane's LDS read offsets within slot 0 (of its key group): K
+  // fragment k of block 0 (row col, chunk 2 k + half) and the transpose read
+  // of dim block c (key row tr_row); the other slots, blocks and key rows of
+  // the product are immediates, as the swizzles repeat every 16 rows.
+  constexpr int kV0 = (KG == 1 ? kRing : 2 * KG) * kSlot;   // first V slot
   int k_rd[D / 16], v_rd[D / 32];
 #pragma unroll
-  for (int k = 0; k < D / 16; ++k) k_rd[k] = col * G_::kRowBytes + (((2 * k + half) ^ G_::swz_k(col)) << 4);
+  for (int k = 0; k < D / 16; ++k) k_rd[k] = kg * kSlot + col * G_::kRowBytes + (((2 * k + half) ^ G_::swz_k(col)) << 4);
   {
     const int tr_row = 4 * half + ((lane & 15) >> 2);
     const int lo = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
 #pragma unroll
     for (int c = 0; c < D / 32; ++c)
-      v_rd[c] = tr_row * G_::kRowBytes + (((4 * c + lo) ^ G_::swz_v(tr_row)) << 4) + 8 * (lane & 1);
+      v_rd[c] = kV0 + kg * kSlot + tr_row * G_::kRowBytes + (((4 * c + lo) ^ G_::swz_v(tr_row)) << 4) + 8 * (lane & 1);
   }
   // Regular-cache item: key k of the sequence is row k mod B of local
   // block rc_ids[rc_off + k / B], read in place.  A wave's rows start on a
@@ -515,11 +536,16 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
       return rc_ids_c[min(k_begin + t * TK + my_row, k_end - 1) >> a.block_shift];
     }
   };
-  // This wave's rows of tile t, K (kV false) or V, into `slot`.  The
-  // buffer resource ends after the last row of the item's range (of the
-  // block, for a regular-cache item), so rows past it, and whole tiles
-  // past the last one, load zeros without touching memory.
-  auto dma = [&](unsigned char *slot, int t, auto v_tag, int blk) {
+  // Slot S (a stage, for narrow items) of this wave's tiles: an offset that
+  // the LDS reads take as an immediate.
+  auto slot_off = [](auto S) { return KG == 1 ? decltype(S)::value % kRing * kSlot : decltype(S)::value % 2 * KG * kSlot; };
+  const uint32_t my_lds =
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_address(ring + kg * kSlot + my_row * G_::kRowBytes));
+  // This wave's rows of tile t, K (kV false) or V, into the slot at offset
+  // `slot`.  The buffer resource ends after the last row of the item's range
+  // (of the block, for a regular-cache item), so rows past it, and whole
+  // tiles past the last one, load zeros without touching memory.
+  auto dma = [&](int slot, int t, auto v_tag, int blk) {
     constexpr bool kV = decltype(v_tag)::value;
     const int key = k_begin + t * TK + my_row;
     const char *base;
@@ -535,31 +561,36 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
       // on the scalar unit.  A 64-bit compare would be a vector
       // instruction whose result the scalar select then waits for (~2%
       // of the loop), as would a saturating unsigned subtract.
-      // At head_dim 64 the tiles past the end would reach further than that
-      // margin: they all load from the first one, past the range as well.
-      const int off = (NB == 1 ? t : min(t, n)) * (int)tile_bytes + my_row * row_bytes;
+      // At head_dim 64 and for narrow items the tiles past the end would
+      // reach further than that margin: they all load from the first one,
+      // past the range as well.
+      const int off = (NB == 1 && KG == 1 ? t : min(t, n)) * (int)tile_bytes + my_row * row_bytes;
       base = reinterpret_cast<const char *>(kV ? vb : kb) + off;
       range = max((int)range_bytes - off, 0);
     }
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char *>(base), (short)0, __builtin_amdgcn_readfirstlane(range), 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(slot + my_row * G_::kRowBytes), 16,
-                                             kV ? voff_v : voff_k, 0, 0, 0);
+    const uint64_t ad = reinterpret_cast<uint64_t>(base);
+    const u32x4 rs = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ad),
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ad >> 32) & 0xffff),
+                      (uint32_t)__builtin_amdgcn_readfirstlane(range), 0x00020000u};
+#pragma unroll
+    for (int i = 0; i < KG; ++i)
+      load_to_lds(my_lds + slot + (kV ? kV0 : 0) + 1024 * i,
+                  kV ? voff_v + i * G_::kRowsPerLoad * row_bytes : voff_k[i], rs);
   };
-  auto qk = [&](const unsigned char *slot, f32x16 (&s)[NB]) {
+  auto qk = [&](int slot, f32x16 (&s)[NB]) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int k = 0; k < D / 16; ++k)
-        s[b] = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(slot + k_rd[k] + 32 * b * G_::kRowBytes), w.qf[k],
+        s[b] = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(ring + k_rd[k] + (slot + 32 * b * G_::kRowBytes)), w.qf[k],
                               k == 0 ? f32x16{} : s[b]);
   };
   // V^T operand of PV step (t, c): dims 32 c .. 32 c + 31 of keys
   // 16 t + [0, 16); k-slot e of a lane in half `half` holds key
   // 16 t + 4 half + (e < 4 ? e : e + 4), which is accumulator element
   // 8 (t mod 2) + e of S^T block t / 2, i.e. pf[t] element e.
-  auto v_operand = [&](const unsigned char *slot, int t, int c) -> u32x4 {
-    const unsigned char *p = slot + v_rd[c] + 16 * t * G_::kRowBytes;
+  auto v_operand = [&](int slot, int t, int c) -> u32x4 {
+    const unsigned char *p = ring + v_rd[c] + (slot + 16 * t * G_::kRowBytes);
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 8 * G_::kRowBytes));
     u32x4 vw;
@@ -570,29 +601,45 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
     return vw;
   };
   // O^T += V^T . P^T.
-  auto pv = [&](const unsigned char *slot, const u32x4 (&pfp)[2 * NB]) {
+  auto pv = [&](int slot, const u32x4 (&pfp)[2 * NB]) {
 #pragma unroll
     for (int t = 0; t < 2 * NB; ++t)
 #pragma unroll
       for (int c = 0; c < D / 32; ++c) w.oacc[c] = Elem<DT>::mfma(v_operand(slot, t, c), pfp[t], w.oacc[c]);
   };
 
-  if (n > 0 && !timed_out) {
-    using T = std::true_type;
-    using F = std::false_type;
-    constexpr int A = kDmaAhead;
-    constexpr int R = kDmaRing;
+  using T = std::true_type;
+  using F = std::false_type;
+  if (KG > 1 && rb * 32 >= wi.nq * group && n > 0 && !timed_out) {
+    // A narrow item of at most 32 rows leaves the second row block's waves
+    // without rows: they load their halves of the tiles and leave the
+    // matrix pipe to the others (same barriers as below).
+    dma(0, kg, F(), 0);
+    dma(KG * kSlot, KG + kg, F(), 0);
+    dma(0, kg, T(), 0);
+    dma(KG * kSlot, KG + kg, T(), 0);
+    dma_barrier<3 * KG>();
+    dma_barrier<2 * KG>();
+    for (int j = 0; j < n_it; ++j) {
+      dma((j & 1) * KG * kSlot, (j + 2) * KG + kg, F(), 0);
+      if (j >= 2) dma((j & 1) * KG * kSlot, j * KG + kg, T(), 0);
+      dma_barrier<0>();
+    }
+  } else if (n > 0 && !timed_out) {
+    constexpr int R = KG == 1 ? kRing : 2;
+#define SC_IC(x) std::integral_constant<int, (x)>()
     // Regular-cache block indices of the tiles the current pair loads into
     // K (bk0, bk1) and V (bv0, bv1), and of the next pair's K tiles.  The
     // V tiles of a pair are the K tiles of the pair before.
-    int bv0 = blk_of(2 * A - 1), bv1 = blk_of(2 * A), bk0 = blk_of(2 * A + 1), bk1 = blk_of(2 * A + 2);
+    int bv0 = blk_of(1), bv1 = blk_of(2), bk0 = blk_of(3), bk1 = blk_of(4);
     int bn0 = 0, bn1 = 0;
-    // Prologue: K(0 .. 2A) and V(0 .. 2A-2), the operands of the first A
-    // pairs, and this wave's Q; then QK(0) once K(0) and Q have landed.  The
-    // first pair loads into the slot QK(0) reads: a second barrier.  K(0) is
-    // the first load issued, before anything that waits for memory, so that
-    // its latency and Q's pass together.
-    dma(dma_k_slot<0>(), 0, F(), blk_of(0));
+    // Prologue: K(0), K(1), K(2) and V(0), the operands of the first pair
+    // (narrow: K(0), K(1), V(0) and V(1), all that a short range has, so that
+    // its loads share one memory latency), and this wave's Q; then QK(0) once K(0) and Q have landed.  The first loads of the loop
+    // go into the slot QK(0) reads: a second barrier.  K(0) is the first load
+    // issued, before anything that waits for memory, so that its latency and
+    // Q's pass together.
+    dma(slot_off(SC_IC(0)), kg, F(), blk_of(0));
     __builtin_amdgcn_sched_barrier(0);
     // Q^T fragments (B operand): lane holds Q[row][16 k + 8 half .. + 7].
     // The buffer resource covers the item's query rows; rows of the
@@ -608,28 +655,37 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
         w.qf[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(qr, qo + 32 * k, 0, 0));
     }
     __builtin_amdgcn_sched_barrier(0);
-    static_for<1, 2 * A + 1>([&](auto t) { dma(dma_k_slot<decltype(t)::value % R>(), t, F(), blk_of(t)); });
-    static_for<0, 2 * A - 1>([&](auto t) { dma(dma_v_slot<decltype(t)::value % R>(), t, T(), blk_of(t)); });
-    dma_barrier<4 * A - 1>();
-    qk(dma_k_slot<0>(), w.s[0]);
-    dma_barrier<0>();
+    if constexpr (KG == 1) {
+      dma(slot_off(SC_IC(1)), 1, F(), blk_of(1));
+      dma(slot_off(SC_IC(2)), 2, F(), blk_of(2));
+      dma(slot_off(SC_IC(0)), 0, T(), blk_of(0));
+      dma_barrier<3>();
+    } else {
+      dma(slot_off(SC_IC(1)), KG + kg, F(), 0);
+      dma(slot_off(SC_IC(0)), kg, T(), 0);
+      dma(slot_off(SC_IC(1)), KG + kg, T(), 0);
+      dma_barrier<3 * KG>();
+    }
+    qk(slot_off(SC_IC(0)), w.s[0]);
+    dma_barrier<KG == 1 ? 0 : 2 * KG>();
 
     // Iteration j (J = j mod R is the ring slot of tile j; tile j's scores
     // live in s[j mod 2]).  Pair p = iterations 2p, 2p+1 reads K(2p+1),
     // K(2p+2), V(2p-1), V(2p).  Its even iteration loads the operands of
-    // pair p+A: K(j+1+2A), K(j+2+2A), V(j-1+2A), V(j+2A), into the slots
-    // last read in pair p-1; its odd iteration ends with a barrier once
-    // the loads issued A-1 pairs earlier have landed, so a load has A
-    // pairs of iterations to land and only every second iteration waits
-    // at a barrier.  Loads of tiles past the last one load zeros.  QK(j+1)
-    // runs in every iteration, also the last, whose product of a stale
-    // slot is never used: one body throughout keeps the MFMA accumulators
-    // in place.
+    // pair p+1: K(j+3), K(j+4), V(j+1), V(j+2), into the slots last read in
+    // pair p-1; its odd iteration ends with a barrier once they have landed,
+    // so only every second iteration waits at a barrier.  A narrow item's
+    // iteration j (its j-th tile) loads K(j+2) and, from j = 2 on, V(j) into
+    // the stage last read in iteration j-1 and ends with that barrier itself.  Loads of
+    // tiles past the last one load zeros.  QK(j+1) runs in every iteration,
+    // also the last, whose product of a stale slot is never used: one body
+    // throughout keeps the MFMA accumulators in place.
     auto iterate = [&](auto j_tag, auto mask_tag, auto first_tag, int j) {
       constexpr int J = decltype(j_tag)::value;
       constexpr bool kMask = decltype(mask_tag)::value;
       constexpr bool kFirst = decltype(first_tag)::value;
       constexpr int PAR = J & 1;
+      const bool late_v = KG > 1 && !kFirst && j >= 2;   // narrow: the prologue loaded V(0) and V(1)
       f32x16 (&sc)[NB] = w.s[PAR];
       f32x16 (&sn)[NB] = w.s[PAR ^ 1];
       if constexpr (kMask) apply_mask(sc, lim_of(j));
@@ -638,8 +694,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
         w.m_run = tm > -INFINITY ? tm : 0.f;
       }
       const float mneg = -w.m_run;
-      const unsigned char *ks = dma_k_slot<(J + 1) % R>();
-      const unsigned char *vs = dma_v_slot<(J + R - 1) % R>();
+      const int ks = slot_off(SC_IC(J + 1));
+      const int vs = slot_off(SC_IC(J + R - 1));
       // The 16 MFMAs of the iteration alternate between QK(j+1) (even
       // steps; block b varies fastest, so no two successive ones depend on
       // each other at head_dim 64) and PV(j-1) (odd steps, V^T block c of
@@ -652,7 +708,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
       auto operand = [&](int i) -> u32x4 {
         const int h = i >> 1;
         if ((i & 1) == 0)
-          return *reinterpret_cast<const u32x4 *>(ks + k_rd[h / NB] + 32 * (h % NB) * G_::kRowBytes);
+          return *reinterpret_cast<const u32x4 *>(ring + k_rd[h / NB] + (ks + 32 * (h % NB) * G_::kRowBytes));
         return v_operand(vs, h / NC, h % NC);
       };
       u32x4 op[16];
@@ -695,21 +751,26 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
           rsum0 += x0;
           rsum1 += x1;
         }
-        if constexpr (PAR == 0) {
-          if (i == 1) dma(dma_k_slot<(J + 1 + 2 * A) % R>(), j + 1 + 2 * A, F(), bk0);
-          if (i == 3) dma(dma_k_slot<(J + 2 + 2 * A) % R>(), j + 2 + 2 * A, F(), bk1);
-          if (i == 5) dma(dma_v_slot<(J - 1 + 2 * A) % R>(), j - 1 + 2 * A, T(), bv0);
-          if (i == 7) dma(dma_v_slot<(J + 2 * A) % R>(), j + 2 * A, T(), bv1);
-          if (i == 9) bn0 = blk_of(j + 3 + 2 * A);
-          if (i == 11) bn1 = blk_of(j + 4 + 2 * A);
+        if constexpr (KG > 1) {
+          if (i == 1) dma(slot_off(SC_IC(J)), (j + 2) * KG + kg, F(), 0);
+          if (i == 3 && late_v) dma(slot_off(SC_IC(J)), j * KG + kg, T(), 0);
+        } else if constexpr (PAR == 0) {
+          if (i == 1) dma(slot_off(SC_IC(J + 3)), j + 3, F(), bk0);
+          if (i == 3) dma(slot_off(SC_IC(J + 4)), j + 4, F(), bk1);
+          if (i == 5) dma(slot_off(SC_IC(J + 1)), j + 1, T(), bv0);
+          if (i == 7) dma(slot_off(SC_IC(J + 2)), j + 2, T(), bv1);
+          if (i == 9) bn0 = blk_of(j + 5);
+          if (i == 11) bn1 = blk_of(j + 6);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
       float rs = rsum0 + rsum1;
       if (!kFirst && __builtin_amdgcn_ballot_w64(!(rs <= Elem<DT>::kSumLimit))) rs = settle_max<D, DT>(w, sc, pf, sl2);
       w.l_run += rs;
-      if constexpr (PAR == 1) {
-        dma_barrier<4 * (A - 1)>();
+      if constexpr (KG > 1) {
+        dma_barrier<0>();
+      } else if constexpr (PAR == 1) {
+        dma_barrier<0>();
         bv0 = bk0;
         bv1 = bk1;
         bk0 = bn0;
@@ -720,23 +781,28 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
     // max), then whole rounds of R unmasked tiles, then the rest masked.
     iterate(std::integral_constant<int, 0>(), T(), T(), 0);
     static_for<1, R>([&](auto J) {
-      if (decltype(J)::value < n) iterate(J, T(), F(), decltype(J)::value);
+      if (decltype(J)::value < n_it) iterate(J, T(), F(), decltype(J)::value);
     });
     int j = R;
-    const int jm = min(j_mask, n);
-    for (; j + R - 1 < jm; j += R) static_for<0, R>([&](auto J) { iterate(J, F(), F(), j + decltype(J)::value); });
-    for (; j < n; j += R)
+    const int jm = min(j_mask, n_it);
+    // (Narrow items at head_dim 64 mask every tile: a second copy of the
+    // loop body takes them from 226 to 242 registers, which leaves no room
+    // for a copy workgroup beside them.)
+    if constexpr (KG == 1 || D == 128)
+      for (; j + R - 1 < jm; j += R) static_for<0, R>([&](auto J) { iterate(J, F(), F(), j + decltype(J)::value); });
+    for (; j < n_it; j += R)
       static_for<0, R>([&](auto J) {
-        if (j + decltype(J)::value < n) iterate(J, T(), F(), j + decltype(J)::value);
+        if (j + decltype(J)::value < n_it) iterate(J, T(), F(), j + decltype(J)::value);
       });
-    // PV of the last tile; its V landed before the last pair's barrier.
-    const int last = (n - 1) % R;
+    // PV of the last tile; its V landed before the last barrier.
+    const int last = (n_it - 1) % R;
     static_for<0, R>([&](auto S) {
       constexpr int kS = decltype(S)::value;
-      if (last == kS) pv(dma_v_slot<kS>(), w.pfb[kS & 1]);   // R is even: kS has the parity of n-1
+      if (last == kS) pv(slot_off(S), w.pfb[kS & 1]);   // R is even: kS has the parity of n_it - 1
     });
     // Loads of tiles past the end may still be in flight.
     dma_wait_all();
+#undef SC_IC
   }
 
   // Done with K/V: every load of it has been consumed (loads past the range
@@ -749,7 +815,72 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const WorkItem &wi,
   }
 
   // Combine the two halves' denominators and normalise.
-  const float l_tot = w.l_run + __shfl_xor(w.l_run, 32);
+  float l_tot = w.l_run + __shfl_xor(w.l_run, 32);
+  if constexpr (KG > 1) {
+    // Combine the key groups: every wave leaves its O (fp32, unnormalised),
+    // reference max and denominator in LDS, and wave kg of a row block
+    // finishes the 16-dim pieces kg, kg + 4 of its rows.  2 KiB per piece,
+    // its two register quads 1 KiB apart.
+    constexpr int NP = D / 16;
+    auto piece = [&](int g, int p) -> unsigned char * {
+      return ring + (rb * KG + g) * 2 * kSlot + p * 2048 + lane * 16;
+    };
+    dma_barrier<0>();   // every wave is done with the tiles
+    const bool has_rows = rb * 32 < wi.nq * group;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (!has_rows) break;
+        const f32x16 &o = w.oacc[p >> 1];
+        const int e = 8 * (p & 1) + 4 * q;
+        *reinterpret_cast<f32x4 *>(piece(kg, p) + 1024 * q) = f32x4{o[e], o[e + 1], o[e + 2], o[e + 3]};
+      }
+    if (half == 0) narrow_ml[rb * KG + kg][col] = f32x2{w.m_run, l_tot};
+    __syncthreads();
+    if (!has_rows) return;
+    // A group without a visible key has l = 0 and an arbitrary reference.
+    float wg[KG], m = -INFINITY;
+    f32x2 ml[KG];
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+      ml[g] = narrow_ml[rb * KG + g][col];
+      if (ml[g][1] != 0.f) m = fmaxf(m, ml[g][0]);
+    }
+    l_tot = 0.f;
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+      wg[g] = ml[g][1] != 0.f ? __builtin_amdgcn_exp2f(ml[g][0] - m) : 0.f;
+      l_tot += wg[g] * ml[g][1];
+    }
+    const float inv = timed_out ? __builtin_nanf("") : l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float lse_val = timed_out ? __builtin_nanf("")
+                          : l_tot > 0.f ? (m + __log2f(l_tot)) * 0.69314718055994530942f : -INFINITY;
+    const int64_t prow = (int64_t)wi.split * a.total_q * a.n_q_heads + qrow;
+    uint16_t *const dst = sd.n_splits == 1 ? a.out + io_row * D : a.part_o + prow * D;
+#pragma unroll
+    for (int i = 0; i < (NP + KG - 1) / KG; ++i) {
+      const int p = kg + i * KG;
+      float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int g = 0; g < KG; ++g)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const f32x4 o = *reinterpret_cast<const f32x4 *>(piece(g, p) + 1024 * q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[4 * q + e] += wg[g] * o[e];
+        }
+      if (valid) store_chunk<DT>(x, inv, dst + 16 * p + 8 * half);
+    }
+    if (valid && half == 0 && kg == 0) {
+      if (sd.n_splits == 1) {
+        if (a.lse != nullptr) a.lse[(int64_t)h * a.total_q + sd.cu_q + qpos] = lse_val;
+      } else {
+        a.part_lse[prow] = lse_val;
+      }
+    }
+    return;
+  }
   const float inv = timed_out ? __builtin_nanf("") : l_tot > 0.f ? 1.f / l_tot : 0.f;
   const float lse_val = timed_out ? __builtin_nanf("")
                         : l_tot > 0.f ? (w.m_run + __log2f(l_tot)) * 0.69314718055994530942f : -INFINITY;
@@ -914,8 +1045,9 @@ __device__ __forceinline__ WorkItem implicit_item(const AttnArgs &a, int w) {
   return wi;
 }
 
-template <int D, int DT>
+template <int D, int DT, bool kNarrow>
 __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[(kNarrow ? 4 * kNarrowGroups : 2 * kRing) * kSlot];
   AttnItem it;
   if (a.items != nullptr)
     it = load_const(a.items + blockIdx.x);
@@ -929,17 +1061,27 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
       __hip_atomic_fetch_add(a.done_counter, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  if (wi.paged)
-    attn_item<D, DT, true>(a, wi, it.sd);
-  else
-    attn_item<D, DT, false>(a, wi, it.sd);
+  if (wi.paged) {
+    attn_item<D, DT, true, 1>(a, ring, wi, it.sd);
+    return;
+  }
+  if constexpr (kNarrow) {
+    if (wi.nq * a.group <= a.narrow_rows) {
+      attn_item<D, DT, false, kNarrowGroups>(a, ring, wi, it.sd);
+      return;
+    }
+  }
+  attn_item<D, DT, false, 1>(a, ring, wi, it.sd);
 }
 
 // One work item per workgroup, then (in a layer stack with deferred
 // merges) its share of the previous layer's merge.
-template <int D, int DT>
+// kNarrow: for plans with narrow items.  Plans without (every query tile
+// full or nearly so) run the kernel without their body: with it, the 8B-shape
+// stack ran 0.4% slower (a longer start, six more registers).
+template <int D, int DT, bool kNarrow>
 __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnArgs a) {
-  attn_fwd_body<D, DT>(a);
+  attn_fwd_body<D, DT, kNarrow>(a);
   if (a.dm_out != nullptr) deferred_merge<D, DT>(a);
 }
 
@@ -987,47 +1129,47 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes) {
   return hipSuccess;
 }
 
+namespace {
+using FwdKernel = void (*)(AttnArgs);
+FwdKernel fwd_kernel(int head_dim, int dtype, bool narrow) {
+  if (head_dim == 128) {
+    if (dtype == SC_DTYPE_F16)
+      return narrow ? attn_fwd_kernel<128, SC_DTYPE_F16, true> : attn_fwd_kernel<128, SC_DTYPE_F16, false>;
+    return narrow ? attn_fwd_kernel<128, SC_DTYPE_BF16, true> : attn_fwd_kernel<128, SC_DTYPE_BF16, false>;
+  }
+  if (dtype == SC_DTYPE_F16)
+    return narrow ? attn_fwd_kernel<64, SC_DTYPE_F16, true> : attn_fwd_kernel<64, SC_DTYPE_F16, false>;
+  return narrow ? attn_fwd_kernel<64, SC_DTYPE_BF16, true> : attn_fwd_kernel<64, SC_DTYPE_BF16, false>;
+}
+}  // namespace
+
 hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_items, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  const dim3 grid(n_items), block(kThreads);
-  if (head_dim == 128) {
-    if (a.dtype == SC_DTYPE_F16)
-      hipLaunchKernelGGL((attn_fwd_kernel<128, SC_DTYPE_F16>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((attn_fwd_kernel<128, SC_DTYPE_BF16>), grid, block, 0, stream, a);
-  } else {
-    if (a.dtype == SC_DTYPE_F16)
-      hipLaunchKernelGGL((attn_fwd_kernel<64, SC_DTYPE_F16>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((attn_fwd_kernel<64, SC_DTYPE_BF16>), grid, block, 0, stream, a);
-  }
+  hipLaunchKernelGGL(fwd_kernel(head_dim, a.dtype, a.narrow_rows > 0), dim3(n_items), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
 int attn_fwd_vgprs(int head_dim) {
-  // The largest of the two element types' kernels for this head_dim.
+  // The largest of this head_dim's kernels (element types, item kinds).
   int m = -1;
-  for (const void *f : {head_dim == 128 ? reinterpret_cast<const void *>(&attn_fwd_kernel<128, SC_DTYPE_BF16>)
-                                        : reinterpret_cast<const void *>(&attn_fwd_kernel<64, SC_DTYPE_BF16>),
-                        head_dim == 128 ? reinterpret_cast<const void *>(&attn_fwd_kernel<128, SC_DTYPE_F16>)
-                                        : reinterpret_cast<const void *>(&attn_fwd_kernel<64, SC_DTYPE_F16>)}) {
-    hipFuncAttributes at{};
-    if (hipFuncGetAttributes(&at, f) != hipSuccess) return -1;
-    m = at.numRegs > m ? at.numRegs : m;
-  }
+  for (int dtype : {SC_DTYPE_BF16, SC_DTYPE_F16})
+    for (bool narrow : {false, true}) {
+      hipFuncAttributes at{};
+      if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(fwd_kernel(head_dim, dtype, narrow))) != hipSuccess)
+        return -1;
+      m = at.numRegs > m ? at.numRegs : m;
+    }
   return m;
 }
 
-size_t attn_fwd_lds_bytes(int head_dim) {
+size_t attn_fwd_lds_bytes(int head_dim, bool narrow) {
   // The largest static LDS of the two element types' kernels; the full LDS
   // of a CU if the runtime cannot tell.
   size_t m = 0;
-  for (const void *f : {head_dim == 128 ? reinterpret_cast<const void *>(&attn_fwd_kernel<128, SC_DTYPE_BF16>)
-                                        : reinterpret_cast<const void *>(&attn_fwd_kernel<64, SC_DTYPE_BF16>),
-                        head_dim == 128 ? reinterpret_cast<const void *>(&attn_fwd_kernel<128, SC_DTYPE_F16>)
-                                        : reinterpret_cast<const void *>(&attn_fwd_kernel<64, SC_DTYPE_F16>)}) {
+  for (int dtype : {SC_DTYPE_BF16, SC_DTYPE_F16}) {
     hipFuncAttributes at{};
-    if (hipFuncGetAttributes(&at, f) != hipSuccess) return (size_t)160 << 10;
+    if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(fwd_kernel(head_dim, dtype, narrow))) != hipSuccess)
+      return (size_t)160 << 10;
     m = at.sharedSizeBytes > m ? at.sharedSizeBytes : m;
   }
   return m;

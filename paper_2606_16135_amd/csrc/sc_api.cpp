@@ -80,7 +80,7 @@ constexpr int64_t kMergeOverheadKeys = 64;  // partial write of a split item, in
 // workgroup's range costs ~33 ns: the 8B shape's merge (16384 rows, 4
 // splits) takes ~5.8 us, the 16-conversation batch's (~520k row-splits)
 // ~33 us.
-constexpr int64_t kMergeLaunchKeys = 45;
+constexpr int64_t kMergeLaunchKeys = 120;
 constexpr int64_t kMergeRowSplitsPerKey = 600;  // (rows x (splits + 1)) per key of merge time
 // Every item also reads its Q tile and writes its output or partial tile
 // (256 rows each way, 128 KiB at head_dim 128), and that traffic shares HBM
@@ -91,6 +91,44 @@ constexpr int64_t kMergeRowSplitsPerKey = 600;  // (rows x (splits + 1)) per key
 // short turns (P <= 4096, N <= 256) run 10-35% faster than with a 512-key
 // floor and no such term.
 constexpr int64_t kItemSharedKeys = 1;
+// A narrow item (few rows, see attn_item) takes 128 keys in an iteration
+// that costs about 1.4 of an ordinary one's 32, and pays for the start of
+// four tiles at once and the combination of its key groups: about 1.7 us
+// with one row block, 3.4 with two (P=1024, N=16 of 32/8 heads, 64 rows:
+// 10.5 us with ordinary items, 11.7 narrow; P=2048, N=8, 32 rows: 11.4 and
+// 10.0).
+constexpr int64_t kNarrowKeys = 4 * kAttnKeyTile;
+constexpr int64_t kNarrowIterationKeys = 44;
+constexpr int64_t kNarrowOverheadKeys[2] = {55, 110};
+// The widest items a plan runs narrow: none, those of one row block, or of
+// two.  Ties go to one row block: the tail tile of a longer turn rarely sets
+// the schedule's length, but narrow it takes a third of the time and leaves
+// the rest of the chip its bandwidth and power (256 tokens of 40/8 heads at
+// P=16384, whose sixth tile has 5 rows: 86.5 us against 91.5).  Two have to
+// shorten the schedule (a batch of 16-19 tokens a sequence, one of them
+// narrow for nothing: 39.3 us a layer against 38.2).
+constexpr int kNarrowChoices[3] = {0, kAttnNarrowRows / 2, kAttnNarrowRows};
+constexpr int kNarrowOrder[3] = {1, 0, 2};
+
+// Cost of an item in keys of an ordinary workgroup's range.
+int64_t item_cost(int64_t keys, int rows, bool paged, bool split, int narrow_rows) {
+  int64_t c = kItemOverheadKeys + (split ? kMergeOverheadKeys : 0);
+  if (rows <= narrow_rows && !paged)
+    c += kNarrowOverheadKeys[rows > kNarrowChoices[1]] +
+         (keys + kNarrowKeys - 1) / kNarrowKeys * kNarrowIterationKeys;
+  else
+    c += keys;
+  return c;
+}
+
+// Whether a plan needs to consider this choice: some tile's rows fall
+// between the next narrower one and it.  Query tiles have `full` rows but
+// for the last of a sequence, which has `last`.
+bool narrow_matters(int choice, int last_rows, int full_rows, bool has_full) {
+  if (choice == 0) return true;
+  const int lo = kNarrowChoices[choice - 1], hi = kNarrowChoices[choice];
+  return (last_rows > lo && last_rows <= hi) || (has_full && full_rows > lo && full_rows <= hi);
+}
 
 struct TileDesc {
   int32_t seq, kvh, q0, nq, keys;
@@ -120,7 +158,7 @@ int64_t lpt_makespan(std::vector<int64_t> &costs, int slots) {
 constexpr int kNoAllocMaxCosts = 4096;
 constexpr int kNoAllocMaxSlots = 2048;
 
-bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out) {
+bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out, int *narrow_rows_out = nullptr) {
   const int group = hq / hkv;
   const int rows_q = kAttnRows / group;
   const int n_qt = (N + rows_q - 1) / rows_q;
@@ -132,48 +170,56 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
     return (int)std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, (max_kv + chunk - 1) / chunk));
   };
   int64_t best_chunk = std::max<int64_t>(max_kv, 1), best_span = -1, best_items = 0;
-  for (int s = 1; s <= kMaxSplits && n_qt > 0; ++s) {
-    int64_t chunk = (max_kv + s - 1) / s;
-    chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
-    if (s > 1 && chunk < kMinSplitKeys) break;
-    if (s > kManySplits && (int64_t)n_qt * hkv * s > slots) break;
-    const int S = splits_of(chunk);
-    if ((int64_t)n_qt * S > kNoAllocMaxCosts) return false;
-    int nc = 0;
-    for (int tile = 0; tile < n_qt; ++tile) {
-      const int q0 = tile * rows_q;
-      const int keys = P + q0 + std::min(rows_q, N - q0);
-      const int t = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
-      for (int sp = 0; sp < S; ++sp) {
-        const int b0 = std::min(keys, (int)((int64_t)sp * t / S) * kAttnKeyTile);
-        const int b1 = std::min(keys, (int)((int64_t)(sp + 1) * t / S) * kAttnKeyTile);
-        costs[nc++] = (std::max(b0, b1) - b0) + kItemOverheadKeys + (S > 1 ? kMergeOverheadKeys : 0);
-      }
-    }
-    const int64_t n = (int64_t)nc * hkv;
-    int64_t makespan = *std::max_element(costs, costs + nc);   // one round of workgroups
-    if (n > slots) {
-      std::sort(costs, costs + nc, std::greater<int64_t>());
-      std::fill(heap, heap + slots, (int64_t)0);   // all zero: already a heap
-      auto cmp = std::greater<int64_t>();
-      for (int i = 0; i < nc; ++i)
-        for (int g = 0; g < hkv; ++g) {
-          std::pop_heap(heap, heap + slots, cmp);
-          heap[slots - 1] += costs[i];
-          std::push_heap(heap, heap + slots, cmp);
+  int best_narrow = 0;
+  const int last_rows = n_qt > 0 ? (N - (n_qt - 1) * rows_q) * group : 0;
+  for (int choice : kNarrowOrder) {
+    if (!narrow_matters(choice, last_rows, rows_q * group, n_qt > 1)) continue;
+    const int narrow_rows = kNarrowChoices[choice];
+    for (int s = 1; s <= kMaxSplits && n_qt > 0; ++s) {
+      int64_t chunk = (max_kv + s - 1) / s;
+      chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
+      if (s > 1 && chunk < kMinSplitKeys) break;
+      if (s > kManySplits && (int64_t)n_qt * hkv * s > slots) break;
+      const int S = splits_of(chunk);
+      if ((int64_t)n_qt * S > kNoAllocMaxCosts) return false;
+      int nc = 0;
+      for (int tile = 0; tile < n_qt; ++tile) {
+        const int q0 = tile * rows_q;
+        const int keys = P + q0 + std::min(rows_q, N - q0);
+        const int t = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
+        for (int sp = 0; sp < S; ++sp) {
+          const int b0 = std::min(keys, (int)((int64_t)sp * t / S) * kAttnKeyTile);
+          const int b1 = std::min(keys, (int)((int64_t)(sp + 1) * t / S) * kAttnKeyTile);
+          costs[nc++] = item_cost(std::max(b0, b1) - b0, std::min(rows_q, N - q0) * group, false, S > 1, narrow_rows);
         }
-      makespan = *std::max_element(heap, heap + slots);
-    }
-    const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
-    const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
-    const int64_t span = makespan + merge + kItemSharedKeys * n;
-    if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
-      best_span = span;
-      best_chunk = chunk;
-      best_items = n;
+      }
+      const int64_t n = (int64_t)nc * hkv;
+      int64_t makespan = *std::max_element(costs, costs + nc);   // one round of workgroups
+      if (n > slots) {
+        std::sort(costs, costs + nc, std::greater<int64_t>());
+        std::fill(heap, heap + slots, (int64_t)0);   // all zero: already a heap
+        auto cmp = std::greater<int64_t>();
+        for (int i = 0; i < nc; ++i)
+          for (int g = 0; g < hkv; ++g) {
+            std::pop_heap(heap, heap + slots, cmp);
+            heap[slots - 1] += costs[i];
+            std::push_heap(heap, heap + slots, cmp);
+          }
+        makespan = *std::max_element(heap, heap + slots);
+      }
+      const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
+      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
+      const int64_t span = makespan + merge + kItemSharedKeys * n;
+      if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
+        best_span = span;
+        best_chunk = chunk;
+        best_items = n;
+        best_narrow = narrow_rows;
+      }
     }
   }
   *splits_out = splits_of(best_chunk);
+  if (narrow_rows_out) *narrow_rows_out = last_rows <= best_narrow || rows_q * group <= best_narrow ? best_narrow : 0;
   return true;
 }
 
@@ -199,7 +245,7 @@ struct GroupItems {
 // Places the items of each (sequence, KV head) group on one XCD (workgroup
 // w runs on XCD w mod 8), groups by decreasing cost onto the least loaded
 // XCD, longest items first within an XCD.
-void place_items(std::vector<GroupItems> &groups, AttnPlan *plan) {
+void place_items(std::vector<GroupItems> &groups, int group, AttnPlan *plan) {
   std::stable_sort(groups.begin(), groups.end(),
                    [](const GroupItems &x, const GroupItems &y) { return x.cost > y.cost; });
   std::vector<int64_t> load(kXcds, 0);
@@ -214,8 +260,9 @@ void place_items(std::vector<GroupItems> &groups, AttnPlan *plan) {
   for (auto &v : per_xcd) {
     // Longest items first; equal costs keep split-major order so that the
     // workgroups resident together read the same key range.
-    std::stable_sort(v.begin(), v.end(), [](const WorkItem &x, const WorkItem &y) {
-      const int cx = x.k_end - x.k_begin, cy = y.k_end - y.k_begin;
+    std::stable_sort(v.begin(), v.end(), [group, plan](const WorkItem &x, const WorkItem &y) {
+      const int64_t cx = item_cost(x.k_end - x.k_begin, x.nq * group, x.paged != 0, false, plan->narrow_rows);
+      const int64_t cy = item_cost(y.k_end - y.k_begin, y.nq * group, y.paged != 0, false, plan->narrow_rows);
       if (cx != cy) return cx > cy;
       if (x.seq != y.seq) return x.seq < y.seq;
       if (x.split != y.split) return x.split < y.split;
@@ -305,31 +352,41 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
   };
   int64_t best_chunk = std::max<int64_t>(max_kv, 1), best_span = -1;
   size_t best_items = 0;
-  for (int s = 1; s <= kMaxSplits && !tiles.empty(); ++s) {
-    int64_t chunk = (max_kv + s - 1) / s;
-    chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
-    if (s > 1 && chunk < kMinSplitKeys) break;
-    if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
-    std::vector<int64_t> costs;
-    std::vector<Range> rs;
-    for (const TileDesc &t : tiles) {
-      ranges_for(chunk, t.seq, t.keys, &rs);
-      const int S = (int)rs.size();
-      for (const Range &r : rs)
-        costs.push_back((r.k_end - r.k_begin) + kItemOverheadKeys + (S > 1 ? kMergeOverheadKeys : 0));
+  for (int choice : kNarrowOrder) {
+    const int narrow_rows = kNarrowChoices[choice];
+    bool matters = false;
+    for (int b = 0; b < batch && !matters; ++b) {
+      const int n_qt = (N[b] + rows_q - 1) / rows_q;
+      matters = n_qt > 0 && narrow_matters(choice, (N[b] - (n_qt - 1) * rows_q) * group, rows_q * group, n_qt > 1);
     }
-    const size_t n = costs.size();
-    int64_t row_splits = 0;
-    for (int b = 0; b < batch; ++b) {
-      const int S = splits_for(chunk, b);
-      if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
-    }
-    const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
-    const int64_t span = lpt_makespan(costs, slots) + merge + kItemSharedKeys * (int64_t)n;
-    if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
-      best_span = span;
-      best_chunk = chunk;
-      best_items = n;
+    if (!matters) continue;
+    for (int s = 1; s <= kMaxSplits && !tiles.empty(); ++s) {
+      int64_t chunk = (max_kv + s - 1) / s;
+      chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
+      if (s > 1 && chunk < kMinSplitKeys) break;
+      if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
+      std::vector<int64_t> costs;
+      std::vector<Range> rs;
+      for (const TileDesc &t : tiles) {
+        ranges_for(chunk, t.seq, t.keys, &rs);
+        const int S = (int)rs.size();
+        for (const Range &r : rs)
+          costs.push_back(item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, S > 1, narrow_rows));
+      }
+      const size_t n = costs.size();
+      int64_t row_splits = 0;
+      for (int b = 0; b < batch; ++b) {
+        const int S = splits_for(chunk, b);
+        if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
+      }
+      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
+      const int64_t span = lpt_makespan(costs, slots) + merge + kItemSharedKeys * (int64_t)n;
+      if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
+        best_span = span;
+        best_chunk = chunk;
+        best_items = n;
+        plan->narrow_rows = narrow_rows;
+      }
     }
   }
   int max_splits = 1;
@@ -360,14 +417,18 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
           w.k_end = rs[s].k_end;
           w.split = s;
           w.paged = rs[s].paged;
-          gi.cost += (w.k_end - w.k_begin) + kItemOverheadKeys;
+          gi.cost += item_cost(w.k_end - w.k_begin, w.nq * group, w.paged != 0, false, plan->narrow_rows);
           gi.items.push_back(w);
         }
       }
       if (!gi.items.empty()) groups.push_back(std::move(gi));
     }
   }
-  place_items(groups, plan);
+  place_items(groups, group, plan);
+  bool narrow = false;
+  for (const WorkItem &w : plan->items)
+    narrow = narrow || (w.seq >= 0 && !w.paged && w.nq * group <= plan->narrow_rows);
+  if (!narrow) plan->narrow_rows = 0;
 }
 
 namespace {
@@ -537,6 +598,7 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
   a.n_kv_heads = hkv;
   a.group = plan.group;
   a.rows_q = plan.rows_q;
+  a.narrow_rows = plan.narrow_rows;
   a.dtype = dtype;
   if (!(scale > 0.f)) scale = 1.f / std::sqrt((float)head_dim);
   a.scale_log2 = scale * 1.4426950408889634f;
@@ -726,7 +788,7 @@ sc_status split_streams(int device, SplitStreams **out) {
 // ---------------------------------------------------------------------------
 constexpr int kCopyBesideAttn = 2;
 std::mutex g_reserve_mu;
-std::map<std::pair<int, int>, size_t> g_reserve;
+std::map<std::tuple<int, int, bool>, size_t> g_reserve;
 
 // Settings under which kernels of different streams do not run at the same
 // time: counter collection by the ROCm profiler serialises dispatches, and
@@ -767,9 +829,9 @@ bool stack_device_wait(const sc_table *t, uint32_t flags) {
   return t->n_fetch_host > 0 || copy_fits_beside_attention(t->pool->desc.head_dim);
 }
 
-size_t copy_lds_reserve(int device, int head_dim) {
+size_t copy_lds_reserve(int device, int head_dim, bool narrow) {
   std::lock_guard<std::mutex> lk(g_reserve_mu);
-  auto key = std::make_pair(device, head_dim);
+  auto key = std::make_tuple(device, head_dim, narrow);
   auto it = g_reserve.find(key);
   if (it != g_reserve.end()) return it->second;
   int lds_cu = 0, lds_block = 0;
@@ -779,7 +841,7 @@ size_t copy_lds_reserve(int device, int head_dim) {
       lds_cu > 0) {
     // kCopyBesideAttn of these fit in the LDS an attention workgroup leaves
     // free, one more does not.
-    const size_t attn = attn_fwd_lds_bytes(head_dim);
+    const size_t attn = attn_fwd_lds_bytes(head_dim, narrow);
     if (attn < (size_t)lds_cu) {
       const size_t cand = (((size_t)lds_cu - attn) / (kCopyBesideAttn + 1) + 1024 + 255) & ~(size_t)255;
       if (cand <= (size_t)lds_block && kCopyBesideAttn * cand + attn <= (size_t)lds_cu) r = cand;
@@ -1599,8 +1661,8 @@ sc_status sc_prefill_attn_noalloc(const void *q, const void *k_active, const voi
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
     cus = 256;
-  int S = 1;
-  if (!single_splits_noalloc(prefix_len, new_len, n_q_heads, n_kv_heads, cus * kResidentPerCu, &S))
+  int S = 1, narrow_rows = 0;
+  if (!single_splits_noalloc(prefix_len, new_len, n_q_heads, n_kv_heads, cus * kResidentPerCu, &S, &narrow_rows))
     return fail(SC_ERR_RANGE, "new turn of %d tokens needs more work items than the allocation-free planner "
                 "holds (%d query tiles x splits)", new_len, kNoAllocMaxCosts);
   void *scr = nullptr;
@@ -1627,6 +1689,7 @@ sc_status sc_prefill_attn_noalloc(const void *q, const void *k_active, const voi
   a.n_kv_heads = n_kv_heads;
   a.group = group;
   a.rows_q = rows_q;
+  a.narrow_rows = narrow_rows;
   a.dtype = SC_DTYPE_BF16;
   if (!(scale > 0.f)) scale = 1.f / std::sqrt((float)head_dim);
   a.scale_log2 = scale * 1.4426950408889634f;
@@ -1911,7 +1974,9 @@ sc_status prefill_stack(sc_pool *pool, const sc_table *table, int32_t n_layers, 
   }
   hipEvent_t *ready = ev, *free_ = ev + 2, start = ev[4], done = ev[5];
   // Host-tier fetches already run on their own CUs (split streams).
-  const size_t reserve = ss ? 0 : copy_lds_reserve(d.device, d.head_dim);
+  bool narrow = false;
+  for (const AttnPlan *pl : plans) narrow = narrow || pl->narrow_rows > 0;
+  const size_t reserve = ss ? 0 : copy_lds_reserve(d.device, d.head_dim, narrow);
   const int groups = ss ? 0 : copy_groups_beside_attention(d.device, table, n_q_heads, d.head_dim);
   // Forward workgroups per layer (every chunk's launch counts itself).
   uint64_t fwd_groups = 0;

@@ -146,6 +146,7 @@ struct AttnArgs {
   int32_t n_kv_heads;
   int32_t group;
   int32_t rows_q;         // queries per workgroup tile
+  int32_t narrow_rows;    // slot items of at most this many rows run narrow (0: none)
   int32_t dtype;          // sc_dtype of q, K, V and out
   float scale_log2;       // softmax scale * log2(e)
   // Optional device-side dependency (overlapped layer stack): before reading
@@ -203,7 +204,8 @@ struct AttnArgs {
 
 // Tile geometry the planner and the kernel agree on.
 constexpr int kAttnRows = 256;   // (query, head) rows per workgroup
-constexpr int kAttnKeyTile = 32; // keys per LDS tile
+constexpr int kAttnKeyTile = 32; // key ranges are cut at multiples of this
+constexpr int kAttnNarrowRows = 64;  // at most this many rows: a narrow item (slot keys only)
 // The attention kernel addresses one sequence's key rows (all KV heads)
 // with signed 32-bit byte offsets, including the loads of up to a few tiles
 // past the last one (which the buffer range turns into zeros): a sequence
@@ -224,7 +226,7 @@ hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_items, hipStre
 // split-key scratch array (looked up once per device, with that device
 // current) and its size in bytes.
 hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes);
-size_t attn_fwd_lds_bytes(int head_dim);
+size_t attn_fwd_lds_bytes(int head_dim, bool narrow);   // narrow: the kernel for plans with narrow items
 int attn_fwd_vgprs(int head_dim);   // per work item, -1 if unknown
 int kv_copy_vgprs();                // largest of the three copy kernels
 hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, int max_splits, hipStream_t stream);
@@ -233,6 +235,7 @@ struct AttnPlan {
   bool paged = false;              // some items read the regular cache in place
   int group = 0;
   int rows_q = 0;
+  int narrow_rows = 0;             // AttnArgs::narrow_rows; 0 when no item is narrow
   int max_splits = 1;
   int n_items = 0;                 // grid size (includes padding slots)
   int n_real_items = 0;

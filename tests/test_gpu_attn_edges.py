@@ -118,3 +118,46 @@ def test_more_than_16_splits_in_a_stack(d):
             compare_attention(to_u16(outs[l]), ref, f"layer {l}")
     finally:
         dp.close()
+
+
+# Narrow items (at most 64 rows of a query tile): one and two row blocks,
+# key counts around their iterations (4 tiles of 32 keys, or of 64 at
+# head_dim 64), alone and as the tail tile of a longer turn, one and several
+# splits.  (N, Hq, Hkv)
+NARROW = [(1, 8, 2), (8, 8, 2), (6, 32, 8), (9, 14, 2), (16, 8, 2), (64, 4, 4), (66, 8, 2), (52, 10, 2), (257, 3, 3)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_narrow_items(d, dtype):
+    sc = require_gpu()
+    for i, (n, hq, hkv) in enumerate(NARROW):
+        for p in (0, 31, 64, 127, 128, 129, 255, 257, 500, 513, 1100, 4000):
+            print(f"[narrow] D={d} {dtype} P={p} N={n} heads {hq}/{hkv}", flush=True)
+            _single(sc, p, n, hq, hkv, d, dtype, 9000 + 100 * i + p)
+
+
+def test_narrow_items_move_their_reference():
+    """Peaky scores: key groups whose references differ by more than the
+    exponent range of a probability, and tile sums that leave the safe range
+    (the reference moves within a group)."""
+    sc = require_gpu()
+    import torch
+    p, n, hq, hkv, d = 700, 7, 8, 2, 128
+    for name, scale in (("growing", 1.0), ("shrinking", -1.0)):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(9999)
+        q = torch.randn((n, hq, d), generator=g, device="cuda").to(torch.bfloat16)
+        k = torch.randn((p + n, hkv, d), generator=g, device="cuda")
+        # Each key leans towards the queries' mean by an amount that grows
+        # (or shrinks) with its position.
+        lean = torch.linspace(-6, 6, p + n, device="cuda")[:, None, None] * scale
+        k = (k + lean * q.float().reshape(n, hkv, hq // hkv, d).mean(dim=(0, 2))[None]).to(torch.bfloat16)
+        v = torch.randn((p + n, hkv, d), generator=g, device="cuda").to(torch.bfloat16)
+        q = (q.float() * 4).to(torch.bfloat16)
+        out = torch.full((n, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        sc.sc_prefill_attn(q.data_ptr(), k.data_ptr(), v.data_ptr(), p, n, hq, hkv, d, out.data_ptr(),
+                           stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        ref, _ = oa.attention(*(bits_to_f64(to_u16(t)) for t in (q, k, v)), [p], [n])
+        compare_attention(to_u16(out), ref, name)
