@@ -134,6 +134,17 @@ struct TileDesc {
   int32_t seq, kvh, q0, nq, keys;
 };
 
+// A schedule of these costs on `slots` slots is no shorter than this: the
+// planners simulate one only where it could still beat the best so far.
+int64_t span_bound(const int64_t *costs, size_t n, int64_t copies, int slots) {
+  int64_t sum = 0, top = 0;
+  for (size_t i = 0; i < n; ++i) {
+    sum += costs[i];
+    top = std::max(top, costs[i]);
+  }
+  return std::max(top, (sum * copies + slots - 1) / std::max(1, slots));
+}
+
 // Longest-processing-time schedule of `costs` on `slots` identical slots.
 int64_t lpt_makespan(std::vector<int64_t> &costs, int slots) {
   if (!costs.empty() && costs.size() <= (size_t)std::max(1, slots)) return *std::max_element(costs.begin(), costs.end());
@@ -158,7 +169,7 @@ int64_t lpt_makespan(std::vector<int64_t> &costs, int slots) {
 constexpr int kNoAllocMaxCosts = 4096;
 constexpr int kNoAllocMaxSlots = 2048;
 
-bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out, int *narrow_rows_out = nullptr) {
+static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out, int *narrow_rows_out) {
   const int group = hq / hkv;
   const int rows_q = kAttnRows / group;
   const int n_qt = (N + rows_q - 1) / rows_q;
@@ -194,6 +205,9 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
         }
       }
       const int64_t n = (int64_t)nc * hkv;
+      const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
+      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
+      if (best_span >= 0 && span_bound(costs, nc, hkv, slots) + merge + kItemSharedKeys * n > best_span) continue;
       int64_t makespan = *std::max_element(costs, costs + nc);   // one round of workgroups
       if (n > slots) {
         std::sort(costs, costs + nc, std::greater<int64_t>());
@@ -207,8 +221,6 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
           }
         makespan = *std::max_element(heap, heap + slots);
       }
-      const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
-      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
       const int64_t span = makespan + merge + kItemSharedKeys * n;
       if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
         best_span = span;
@@ -219,7 +231,32 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
     }
   }
   *splits_out = splits_of(best_chunk);
-  if (narrow_rows_out) *narrow_rows_out = last_rows <= best_narrow || rows_q * group <= best_narrow ? best_narrow : 0;
+  *narrow_rows_out = last_rows <= best_narrow || rows_q * group <= best_narrow ? best_narrow : 0;
+  return true;
+}
+
+// The choice for the shapes this thread called with last: a program makes the
+// same call for every layer, and a long turn's schedule takes longer to
+// simulate than its attention takes to run (P=8192, N=512 of 32/8 heads:
+// about 60 us).
+bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out, int *narrow_rows_out) {
+  struct Choice {
+    int P, N, hq, hkv, slots, splits, narrow_rows;
+  };
+  constexpr int kChoices = 16;
+  static thread_local Choice recent[kChoices] = {};   // hq == 0: empty
+  static thread_local int next = 0;
+  const Choice *c = nullptr;
+  for (const Choice &x : recent)
+    if (x.P == P && x.N == N && x.hq == hq && x.hkv == hkv && x.slots == slots) c = &x;
+  if (c == nullptr) {
+    Choice x{P, N, hq, hkv, slots, 1, 0};
+    if (!choose_splits_noalloc(P, N, hq, hkv, slots, &x.splits, &x.narrow_rows)) return false;
+    c = &(recent[next] = x);
+    next = (next + 1) % kChoices;
+  }
+  *splits_out = c->splits;
+  if (narrow_rows_out) *narrow_rows_out = c->narrow_rows;
   return true;
 }
 
@@ -365,22 +402,28 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
       chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
       if (s > 1 && chunk < kMinSplitKeys) break;
       if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
-      std::vector<int64_t> costs;
+      std::vector<int64_t> costs;   // of one KV head's items; the others' are the same
       std::vector<Range> rs;
       for (const TileDesc &t : tiles) {
+        if (t.kvh != 0) continue;
         ranges_for(chunk, t.seq, t.keys, &rs);
         const int S = (int)rs.size();
         for (const Range &r : rs)
           costs.push_back(item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, S > 1, narrow_rows));
       }
-      const size_t n = costs.size();
+      const size_t n = costs.size() * (size_t)n_kv_heads;
       int64_t row_splits = 0;
       for (int b = 0; b < batch; ++b) {
         const int S = splits_for(chunk, b);
         if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
       }
       const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
-      const int64_t span = lpt_makespan(costs, slots) + merge + kItemSharedKeys * (int64_t)n;
+      const int64_t extra = merge + kItemSharedKeys * (int64_t)n;
+      if (best_span >= 0 && span_bound(costs.data(), costs.size(), n_kv_heads, slots) + extra > best_span) continue;
+      const size_t one = costs.size();
+      costs.resize(n);
+      for (size_t i = one; i < n; ++i) costs[i] = costs[i - one];
+      const int64_t span = lpt_makespan(costs, slots) + extra;
       if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
         best_span = span;
         best_chunk = chunk;
@@ -1719,7 +1762,7 @@ sc_status sc_attn_noalloc_splits(int32_t prefix_len, int32_t new_len, int32_t n_
   if (st != SC_OK) return st;
   int S = 1;
   if (!single_splits_noalloc(prefix_len, new_len, n_q_heads, n_kv_heads, slots > 0 ? slots : kQueryDefaultSlots,
-                             &S))
+                             &S, nullptr))
     return fail(SC_ERR_RANGE, "shape exceeds the allocation-free planner's buffers");
   *splits = S;
   return SC_OK;

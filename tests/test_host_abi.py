@@ -454,3 +454,25 @@ def test_noalloc_argument_validation(sc):
     with pytest.raises(sc.SwiftCacheError) as e:
         sc.sc_attn_noalloc_splits(4, 70000, 32, 8)                   # beyond the fixed buffers
     assert e.value.status == sc.SC_ERR_RANGE
+
+
+def test_noalloc_split_choice_is_the_same_when_asked_again(sc):
+    """The allocation-free planner keeps its last choices per thread: more
+    shapes than it keeps, asked in two orders and from another thread, give
+    what the table planner gives."""
+    import threading
+    shapes = [(64 + 97 * i, 1 + 13 * (i % 23), 8 * (1 + i % 5), 8) for i in range(40)]
+    want = [sc.sc_attn_plan_query([p], [n], hq, hkv, 256)[1][0] for p, n, hq, hkv in shapes]
+    got = []
+
+    def ask():
+        for order in (range(40), reversed(range(40))):
+            for i in order:
+                p, n, hq, hkv = shapes[i]
+                for _ in range(2):
+                    got.append(sc.sc_attn_noalloc_splits(p, n, hq, hkv, 256) == want[i])
+    ask()
+    t = threading.Thread(target=ask)
+    t.start()
+    t.join()
+    assert len(got) == 320 and all(got)
