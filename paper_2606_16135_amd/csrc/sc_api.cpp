@@ -1953,16 +1953,16 @@ sc_status prefill_stack(sc_pool *pool, const sc_table *table, int32_t n_layers, 
   }
 
   // Overlapped.  Attention of layer l waits on the device for the copy
-  // stream's count of filled slots (table->d_sync[0], written by the copy
-  // stream after the layer's copy); a stream-level wait here would put a
-  // command-processor round trip (about 12 us measured) in front of every
-  // attention.  In the other direction the copy stream runs a one-wave gate
-  // kernel that waits until every forward workgroup of the attention that
-  // last read slot s has counted itself done (table->d_sync[2]); fetch,
-  // append and store of the layer then run as one launch.  Per layer that
-  // leaves the host two launches on the copy stream, one counter write and
-  // the attention's launches, where separate copy launches and an event
-  // record plus a cross-stream wait cost about twice as much host time,
+  // stream's count of filled slots (table->d_sync[0]); a stream-level wait
+  // here would put a command-processor round trip (about 12 us measured) in
+  // front of every attention.  Between two layers' copies (fetch, append and
+  // store of a layer as one launch) the copy stream runs a one-wave gate
+  // kernel: it publishes the slot just filled and, in the other direction,
+  // waits until every forward workgroup of the attention that last read the
+  // next slot has counted itself done (table->d_sync[2]).  Per layer that
+  // leaves the host two launches on the copy stream and the attention's,
+  // where separate copy launches and an event record plus a cross-stream
+  // wait cost more than twice as much host time,
   // which bounded short turns.  Without the device wait (a copy workgroup
   // could be kept off a CU by attention) the streams wait on events.
   // Disjoint CU sets (host tier) never block each other.
@@ -2042,13 +2042,6 @@ sc_status prefill_stack(sc_pool *pool, const sc_table *table, int32_t n_layers, 
       const int s = l & 1;
       sc_status r;
       if (device_wait) {
-        // Slot s was last read by attention(l-2): wait for layers 0..l-2.
-        if (l >= 2) {
-          hipError_t e = launch_slot_gate(sync + 2, (uint64_t)(l - 1) * fwd_groups + never_f,
-                                          reinterpret_cast<uint32_t *>(sync + 1), sync + 3, base + l + 1,
-                                          gate_spin, xs);
-          if (e != hipSuccess) return fail_hip(e, "slot gate launch");
-        }
         if (poison && (r = poison_slot(slots[s], xs)) != SC_OK) return r;
         LayerCopyArgs la = layer_copy_args(pool, table, l, knew_per_layer[l], vnew_per_layer[l], &slots[s], do_st);
         la.fail_word = sync + 3;
@@ -2056,7 +2049,13 @@ sc_status prefill_stack(sc_pool *pool, const sc_table *table, int32_t n_layers, 
         la.nan2 = nan2;
         hipError_t e = launch_kv_layer_copy(la, xs, reserve, groups);
         if (e != hipSuccess) return fail_hip(e, "layer copy launch");
-        SC_HIP(hipStreamWriteValue64(xs, sync, base + l + 1, 0));
+        // Publish this slot, then wait for the next layer's: it was last
+        // read by attention(l-1), so for layers 0..l-1.  Enqueued before this
+        // layer's attention, which waits for the publication.
+        const uint64_t free_at = l >= 1 && l + 1 < n_layers ? (uint64_t)l * fwd_groups + never_f : 0;
+        e = launch_slot_gate(sync, base + l + 1, sync + 2, free_at, reinterpret_cast<uint32_t *>(sync + 1), sync + 3,
+                             base + l + 2, gate_spin, xs);
+        if (e != hipSuccess) return fail_hip(e, "slot gate launch");
         if ((r = attn(l, slots[s], sync, base + l + 1, nullptr, sync + 2)) != SC_OK) return r;
         continue;
       }

@@ -83,12 +83,14 @@ struct LayerCopyArgs {
   uint32_t nan2;                   // nan16 repeated in both halves
 };
 hipError_t launch_kv_layer_copy(const LayerCopyArgs &a, hipStream_t stream, size_t lds_reserve, int max_groups);
-// One-wave kernel that holds the stream until *counter >= value (the
-// attention workgroups that read a slot are all done with it), polling at
-// most spin_limit times; on time-out it sets *timeout and *fail_word =
-// fail_tag and ends.  One wave cannot keep an attention workgroup off a CU.
-hipError_t launch_slot_gate(const uint64_t *counter, uint64_t value, uint32_t *timeout, uint64_t *fail_word,
-                            uint64_t fail_tag, int spin_limit, hipStream_t stream);
+// One-wave kernel that sets *filled = filled_value, then holds the stream
+// until *counter >= value (the attention workgroups that read a slot are all
+// done with it; value 0: no wait), polling at most spin_limit times; on
+// time-out it sets *timeout and *fail_word = fail_tag and ends.  One wave
+// cannot keep an attention workgroup off a CU.
+hipError_t launch_slot_gate(uint64_t *filled, uint64_t filled_value, const uint64_t *counter, uint64_t value,
+                            uint32_t *timeout, uint64_t *fail_word, uint64_t fail_tag, int spin_limit,
+                            hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Attention work decomposition
