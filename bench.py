@@ -55,11 +55,11 @@ ROTATE_BYTES = 512 << 20         # destination buffers the standalone fetch cycl
 # with the hash of the attention source's code (comments left out) they were
 # taken on; a stale entry (the code changed since) is reported as null.
 PMC_TRAFFIC = {
-    "llama3-8b-P8192-N512": (80648308, "2e7333fba4a48280"),
-    "llama3-8b-batch16-varlen": (833873150, "2e7333fba4a48280"),
-    "qwen-14b-P32768-N1024": (487705388, "2e7333fba4a48280"),
-    "llama3-8b-P131072-N2048-hosttier": (1191297486, "2e7333fba4a48280"),
-    "llama3-8b-P8192-N512-rc0.5": (79923592, "2e7333fba4a48280"),
+    "llama3-8b-P8192-N512": (80673560, "b3347e5e53f7ac75"),
+    "llama3-8b-batch16-varlen": (833774953, "b3347e5e53f7ac75"),
+    "qwen-14b-P32768-N1024": (487076777, "b3347e5e53f7ac75"),
+    "llama3-8b-P131072-N2048-hosttier": (1190242354, "b3347e5e53f7ac75"),
+    "llama3-8b-P8192-N512-rc0.5": (79949312, "b3347e5e53f7ac75"),
 }
 
 

@@ -202,8 +202,8 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 
-// K/V slots of 8 KiB in the workgroup's `ring`, loaded straight into LDS
-// (see attn_item).  Ordinary items: slot s of the four K slots at 8 s KiB, of
+// K/V slots of 8 KiB, loaded straight into LDS (see attn_item).  Kernels
+// with narrow items keep them in one array, `ring`.  Ordinary items: slot s of the four K slots at 8 s KiB, of
 // the four V slots 32 KiB further.  Narrow items: two stages of four key groups' slots, K at
 // 32 stage + 8 group KiB, V 64 KiB further.  A tile's load has one pair of
 // iterations to land in (one iteration for narrow items); two or three pairs
@@ -213,6 +213,17 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 constexpr int kRing = 4;
 constexpr int kNarrowGroups = 4;
 constexpr int kSlot = Tile<128>::kSlotBytes;
+// The slots of kernels without narrow items: one array per slot and operand,
+// so the compiler can tell that a load in flight into one does not alias
+// reads of another (see load_to_lds).
+#define SC_SLOT(n)                                                              \
+  __shared__ __attribute__((aligned(1024))) unsigned char slot_k##n[kSlot];     \
+  __shared__ __attribute__((aligned(1024))) unsigned char slot_v##n[kSlot];
+SC_SLOT(0)
+SC_SLOT(1)
+SC_SLOT(2)
+SC_SLOT(3)
+#undef SC_SLOT
 // Narrow items: each wave's reference max and row sums (32 rows), for the
 // waves that combine them.
 __shared__ f32x2 narrow_ml[8][32];
@@ -243,10 +254,12 @@ __device__ __forceinline__ void dma_barrier() {
 // One wave's 1 KiB load into LDS at byte address `lds` (in M0 for the
 // instruction, which needs one wait state after the write of M0; nothing
 // else in these kernels uses M0, and saving it cost 0.5-1% of a call).
-// Written out because all slots are one array (narrow items pick theirs at
-// run time): around the builtin the compiler would wait for every load in
-// flight before any LDS read.  The waits are dma_barrier's; there is no
-// output register.
+// Written out for the kernels with narrow items, whose slots are one array
+// (narrow items pick theirs at run time): around the builtin the compiler
+// would wait for every load in flight before any LDS read.  The waits are
+// dma_barrier's; there is no output register.  Kernels without them keep the
+// builtin and an array per slot: the wait states cost 0.4% of a long loop
+// (131072 keys: 3457 us against 3478).
 __device__ __forceinline__ void load_to_lds(uint32_t lds, int voff, u32x4 rsrc) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :
@@ -392,9 +405,9 @@ __device__ __forceinline__ void store_row(const WaveState<D> &w, float inv, int 
 // layer stack of 40/8 heads in chunks of 256 tokens, whose last query tile
 // has 5 rows: 1610 -> 1540 us.  The kinds are separate copies of the whole body so that each is register-allocated on
 // its own.
-template <int D, int DT, bool kPaged, int KG>
+template <int D, int DT, bool kPaged, int KG, bool kNamed>
 __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring, const WorkItem &wi, const SeqDesc &sd) {
-  static_assert(KG == 1 || (KG == kNarrowGroups && !kPaged), "kinds of item");
+  static_assert(KG == 1 || (KG == kNarrowGroups && !kPaged && !kNamed), "kinds of item");
   using G_ = Tile<D>;
   constexpr int NB = G_::kBlocks;
   constexpr int TK = G_::kKeys;      // keys per tile
@@ -498,10 +511,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     voff_k[i] = r * row_bytes + ((c ^ G_::swz_k(my_row + r)) << 4);
     if (i == 0) voff_v = r * row_bytes + ((c ^ G_::swz_v(my_row + r)) << 4);
   }
-  // This lane's LDS read offsets within slot 0 (of its key group): K
+  // This lane's LDS read offsets within a slot (of its key group): K
   // fragment k of block 0 (row col, chunk 2 k + half) and the transpose read
-  // of dim block c (key row tr_row); the other slots, blocks and key rows of
-  // the product are immediates, as the swizzles repeat every 16 rows.
+  // of dim block c (key row tr_row); the slots, blocks and key rows of the
+  // product are immediates, as the swizzles repeat every 16 rows.
   constexpr int kV0 = (KG == 1 ? kRing : 2 * KG) * kSlot;   // first V slot
   int k_rd[D / 16], v_rd[D / 32];
 #pragma unroll
@@ -511,7 +524,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     const int lo = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
 #pragma unroll
     for (int c = 0; c < D / 32; ++c)
-      v_rd[c] = kV0 + kg * kSlot + tr_row * G_::kRowBytes + (((4 * c + lo) ^ G_::swz_v(tr_row)) << 4) + 8 * (lane & 1);
+      v_rd[c] = (kNamed ? 0 : kV0) + kg * kSlot + tr_row * G_::kRowBytes +
+                (((4 * c + lo) ^ G_::swz_v(tr_row)) << 4) + 8 * (lane & 1);
   }
   // Regular-cache item: key k of the sequence is row k mod B of local
   // block rc_ids[rc_off + k / B], read in place.  A wave's rows start on a
@@ -536,16 +550,28 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
       return rc_ids_c[min(k_begin + t * TK + my_row, k_end - 1) >> a.block_shift];
     }
   };
-  // Slot S (a stage, for narrow items) of this wave's tiles: an offset that
-  // the LDS reads take as an immediate.
-  auto slot_off = [](auto S) { return KG == 1 ? decltype(S)::value % kRing * kSlot : decltype(S)::value % 2 * KG * kSlot; };
+  // K and V slot S (a stage, for narrow items).
+  auto k_slot = [&](auto S) -> unsigned char * {
+    constexpr int s = decltype(S)::value;
+    if constexpr (kNamed)
+      return s % kRing == 0 ? slot_k0 : s % kRing == 1 ? slot_k1 : s % kRing == 2 ? slot_k2 : slot_k3;
+    else
+      return ring + (KG == 1 ? s % kRing : s % 2 * KG) * kSlot;
+  };
+  auto v_slot = [&](auto S) -> unsigned char * {
+    constexpr int s = decltype(S)::value;
+    if constexpr (kNamed)
+      return s % kRing == 0 ? slot_v0 : s % kRing == 1 ? slot_v1 : s % kRing == 2 ? slot_v2 : slot_v3;
+    else
+      return ring + (KG == 1 ? s % kRing : s % 2 * KG) * kSlot;   // kV0 further, in v_rd and dma
+  };
   const uint32_t my_lds =
-      (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_address(ring + kg * kSlot + my_row * G_::kRowBytes));
-  // This wave's rows of tile t, K (kV false) or V, into the slot at offset
-  // `slot`.  The buffer resource ends after the last row of the item's range
-  // (of the block, for a regular-cache item), so rows past it, and whole
-  // tiles past the last one, load zeros without touching memory.
-  auto dma = [&](int slot, int t, auto v_tag, int blk) {
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)(kg * kSlot + my_row * G_::kRowBytes));   // within a slot
+  // This wave's rows of tile t, K (kV false) or V, into `slot`.  The buffer
+  // resource ends after the last row of the item's range (of the block, for
+  // a regular-cache item), so rows past it, and whole tiles past the last
+  // one, load zeros without touching memory.
+  auto dma = [&](unsigned char *slot, int t, auto v_tag, int blk) {
     constexpr bool kV = decltype(v_tag)::value;
     const int key = k_begin + t * TK + my_row;
     const char *base;
@@ -568,29 +594,39 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
       base = reinterpret_cast<const char *>(kV ? vb : kb) + off;
       range = max((int)range_bytes - off, 0);
     }
-    const uint64_t ad = reinterpret_cast<uint64_t>(base);
-    const u32x4 rs = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ad),
-                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ad >> 32) & 0xffff),
-                      (uint32_t)__builtin_amdgcn_readfirstlane(range), 0x00020000u};
+    if constexpr (kNamed) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<char *>(base), (short)0, __builtin_amdgcn_readfirstlane(range), 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(slot + my_lds), 16,
+                                               kV ? voff_v : voff_k[0], 0, 0, 0);
+    } else {
+      // The resource's second word holds address bits 32-47 and, above them,
+      // a stride of zero: the address as it is (device addresses have 48
+      // bits).
+      const uint64_t ad = reinterpret_cast<uint64_t>(base);
+      const u32x4 rs = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ad),
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ad >> 32)),
+                        (uint32_t)__builtin_amdgcn_readfirstlane(range), 0x00020000u};
+      const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_address(slot) + my_lds + (kV ? kV0 : 0)));
 #pragma unroll
-    for (int i = 0; i < KG; ++i)
-      load_to_lds(my_lds + slot + (kV ? kV0 : 0) + 1024 * i,
-                  kV ? voff_v + i * G_::kRowsPerLoad * row_bytes : voff_k[i], rs);
+      for (int i = 0; i < KG; ++i)
+        load_to_lds(to + 1024 * i, kV ? voff_v + i * G_::kRowsPerLoad * row_bytes : voff_k[i], rs);
+    }
   };
-  auto qk = [&](int slot, f32x16 (&s)[NB]) {
+  auto qk = [&](const unsigned char *slot, f32x16 (&s)[NB]) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int k = 0; k < D / 16; ++k)
-        s[b] = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(ring + k_rd[k] + (slot + 32 * b * G_::kRowBytes)), w.qf[k],
+        s[b] = Elem<DT>::mfma(*reinterpret_cast<const u32x4 *>(slot + k_rd[k] + 32 * b * G_::kRowBytes), w.qf[k],
                               k == 0 ? f32x16{} : s[b]);
   };
   // V^T operand of PV step (t, c): dims 32 c .. 32 c + 31 of keys
   // 16 t + [0, 16); k-slot e of a lane in half `half` holds key
   // 16 t + 4 half + (e < 4 ? e : e + 4), which is accumulator element
   // 8 (t mod 2) + e of S^T block t / 2, i.e. pf[t] element e.
-  auto v_operand = [&](int slot, int t, int c) -> u32x4 {
-    const unsigned char *p = ring + v_rd[c] + (slot + 16 * t * G_::kRowBytes);
+  auto v_operand = [&](const unsigned char *slot, int t, int c) -> u32x4 {
+    const unsigned char *p = slot + v_rd[c] + 16 * t * G_::kRowBytes;
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 8 * G_::kRowBytes));
     u32x4 vw;
@@ -601,7 +637,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     return vw;
   };
   // O^T += V^T . P^T.
-  auto pv = [&](int slot, const u32x4 (&pfp)[2 * NB]) {
+  auto pv = [&](const unsigned char *slot, const u32x4 (&pfp)[2 * NB]) {
 #pragma unroll
     for (int t = 0; t < 2 * NB; ++t)
 #pragma unroll
@@ -614,15 +650,15 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     // A narrow item of at most 32 rows leaves the second row block's waves
     // without rows: they load their halves of the tiles and leave the
     // matrix pipe to the others (same barriers as below).
-    dma(0, kg, F(), 0);
-    dma(KG * kSlot, KG + kg, F(), 0);
-    dma(0, kg, T(), 0);
-    dma(KG * kSlot, KG + kg, T(), 0);
+    dma(ring, kg, F(), 0);
+    dma(ring + KG * kSlot, KG + kg, F(), 0);
+    dma(ring, kg, T(), 0);
+    dma(ring + KG * kSlot, KG + kg, T(), 0);
     dma_barrier<3 * KG>();
     dma_barrier<2 * KG>();
     for (int j = 0; j < n_it; ++j) {
-      dma((j & 1) * KG * kSlot, (j + 2) * KG + kg, F(), 0);
-      if (j >= 2) dma((j & 1) * KG * kSlot, j * KG + kg, T(), 0);
+      dma(ring + (j & 1) * KG * kSlot, (j + 2) * KG + kg, F(), 0);
+      if (j >= 2) dma(ring + (j & 1) * KG * kSlot, j * KG + kg, T(), 0);
       dma_barrier<0>();
     }
   } else if (n > 0 && !timed_out) {
@@ -635,11 +671,12 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     int bn0 = 0, bn1 = 0;
     // Prologue: K(0), K(1), K(2) and V(0), the operands of the first pair
     // (narrow: K(0), K(1), V(0) and V(1), all that a short range has, so that
-    // its loads share one memory latency), and this wave's Q; then QK(0) once K(0) and Q have landed.  The first loads of the loop
-    // go into the slot QK(0) reads: a second barrier.  K(0) is the first load
+    // its loads share one memory latency), and this wave's Q; then QK(0) once
+    // K(0) and Q have landed.  The first loads of the loop go into the slot
+    // QK(0) reads: a second barrier.  K(0) is the first load
     // issued, before anything that waits for memory, so that its latency and
     // Q's pass together.
-    dma(slot_off(SC_IC(0)), kg, F(), blk_of(0));
+    dma(k_slot(SC_IC(0)), kg, F(), blk_of(0));
     __builtin_amdgcn_sched_barrier(0);
     // Q^T fragments (B operand): lane holds Q[row][16 k + 8 half .. + 7].
     // The buffer resource covers the item's query rows; rows of the
@@ -656,17 +693,17 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     }
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (KG == 1) {
-      dma(slot_off(SC_IC(1)), 1, F(), blk_of(1));
-      dma(slot_off(SC_IC(2)), 2, F(), blk_of(2));
-      dma(slot_off(SC_IC(0)), 0, T(), blk_of(0));
+      dma(k_slot(SC_IC(1)), 1, F(), blk_of(1));
+      dma(k_slot(SC_IC(2)), 2, F(), blk_of(2));
+      dma(v_slot(SC_IC(0)), 0, T(), blk_of(0));
       dma_barrier<3>();
     } else {
-      dma(slot_off(SC_IC(1)), KG + kg, F(), 0);
-      dma(slot_off(SC_IC(0)), kg, T(), 0);
-      dma(slot_off(SC_IC(1)), KG + kg, T(), 0);
+      dma(k_slot(SC_IC(1)), KG + kg, F(), 0);
+      dma(v_slot(SC_IC(0)), kg, T(), 0);
+      dma(v_slot(SC_IC(1)), KG + kg, T(), 0);
       dma_barrier<3 * KG>();
     }
-    qk(slot_off(SC_IC(0)), w.s[0]);
+    qk(k_slot(SC_IC(0)), w.s[0]);
     dma_barrier<KG == 1 ? 0 : 2 * KG>();
 
     // Iteration j (J = j mod R is the ring slot of tile j; tile j's scores
@@ -694,8 +731,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
         w.m_run = tm > -INFINITY ? tm : 0.f;
       }
       const float mneg = -w.m_run;
-      const int ks = slot_off(SC_IC(J + 1));
-      const int vs = slot_off(SC_IC(J + R - 1));
+      const unsigned char *ks = k_slot(SC_IC(J + 1));
+      const unsigned char *vs = v_slot(SC_IC(J + R - 1));
       // The 16 MFMAs of the iteration alternate between QK(j+1) (even
       // steps; block b varies fastest, so no two successive ones depend on
       // each other at head_dim 64) and PV(j-1) (odd steps, V^T block c of
@@ -708,7 +745,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
       auto operand = [&](int i) -> u32x4 {
         const int h = i >> 1;
         if ((i & 1) == 0)
-          return *reinterpret_cast<const u32x4 *>(ring + k_rd[h / NB] + (ks + 32 * (h % NB) * G_::kRowBytes));
+          return *reinterpret_cast<const u32x4 *>(ks + k_rd[h / NB] + 32 * (h % NB) * G_::kRowBytes);
         return v_operand(vs, h / NC, h % NC);
       };
       u32x4 op[16];
@@ -752,13 +789,13 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
           rsum1 += x1;
         }
         if constexpr (KG > 1) {
-          if (i == 1) dma(slot_off(SC_IC(J)), (j + 2) * KG + kg, F(), 0);
-          if (i == 3 && late_v) dma(slot_off(SC_IC(J)), j * KG + kg, T(), 0);
+          if (i == 1) dma(k_slot(SC_IC(J)), (j + 2) * KG + kg, F(), 0);
+          if (i == 3 && late_v) dma(v_slot(SC_IC(J)), j * KG + kg, T(), 0);
         } else if constexpr (PAR == 0) {
-          if (i == 1) dma(slot_off(SC_IC(J + 3)), j + 3, F(), bk0);
-          if (i == 3) dma(slot_off(SC_IC(J + 4)), j + 4, F(), bk1);
-          if (i == 5) dma(slot_off(SC_IC(J + 1)), j + 1, T(), bv0);
-          if (i == 7) dma(slot_off(SC_IC(J + 2)), j + 2, T(), bv1);
+          if (i == 1) dma(k_slot(SC_IC(J + 3)), j + 3, F(), bk0);
+          if (i == 3) dma(k_slot(SC_IC(J + 4)), j + 4, F(), bk1);
+          if (i == 5) dma(v_slot(SC_IC(J + 1)), j + 1, T(), bv0);
+          if (i == 7) dma(v_slot(SC_IC(J + 2)), j + 2, T(), bv1);
           if (i == 9) bn0 = blk_of(j + 5);
           if (i == 11) bn1 = blk_of(j + 6);
         }
@@ -798,7 +835,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     const int last = (n_it - 1) % R;
     static_for<0, R>([&](auto S) {
       constexpr int kS = decltype(S)::value;
-      if (last == kS) pv(slot_off(S), w.pfb[kS & 1]);   // R is even: kS has the parity of n_it - 1
+      if (last == kS) pv(v_slot(S), w.pfb[kS & 1]);   // R is even: kS has the parity of n_it - 1
     });
     // Loads of tiles past the end may still be in flight.
     dma_wait_all();
@@ -1047,7 +1084,6 @@ __device__ __forceinline__ WorkItem implicit_item(const AttnArgs &a, int w) {
 
 template <int D, int DT, bool kNarrow>
 __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char ring[(kNarrow ? 4 * kNarrowGroups : 2 * kRing) * kSlot];
   AttnItem it;
   if (a.items != nullptr)
     it = load_const(a.items + blockIdx.x);
@@ -1061,17 +1097,20 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
       __hip_atomic_fetch_add(a.done_counter, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  if (wi.paged) {
-    attn_item<D, DT, true, 1>(a, ring, wi, it.sd);
-    return;
-  }
   if constexpr (kNarrow) {
-    if (wi.nq * a.group <= a.narrow_rows) {
-      attn_item<D, DT, false, kNarrowGroups>(a, ring, wi, it.sd);
-      return;
-    }
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[4 * kNarrowGroups * kSlot];
+    if (wi.paged)
+      attn_item<D, DT, true, 1, false>(a, ring, wi, it.sd);
+    else if (wi.nq * a.group <= a.narrow_rows)
+      attn_item<D, DT, false, kNarrowGroups, false>(a, ring, wi, it.sd);
+    else
+      attn_item<D, DT, false, 1, false>(a, ring, wi, it.sd);
+  } else {
+    if (wi.paged)
+      attn_item<D, DT, true, 1, true>(a, nullptr, wi, it.sd);
+    else
+      attn_item<D, DT, false, 1, true>(a, nullptr, wi, it.sd);
   }
-  attn_item<D, DT, false, 1>(a, ring, wi, it.sd);
 }
 
 // One work item per workgroup, then (in a layer stack with deferred
