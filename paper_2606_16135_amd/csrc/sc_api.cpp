@@ -70,6 +70,9 @@ constexpr int kMaxSplits = kAttnMaxSplits;
 // the extra partials only add rounds and merge traffic (P=3000, N=100:
 // 11 splits 21 us, 20 splits 60).
 constexpr int kManySplits = 16;
+// ... and where they save more than the wider merge costs (about 1.5 us:
+// 28/4 heads, P=3475, N=32: 16.7 us with 16 splits, 17.2 with 22).
+constexpr int64_t kManySplitsKeys = 45;
 constexpr int kResidentPerCu = 1;        // one 8-wave workgroup per CU (LDS ring, 2 waves per SIMD)
 constexpr int kQueryDefaultSlots = 256 * kResidentPerCu;   // MI355X: 256 CUs
 constexpr int64_t kItemOverheadKeys = 128;  // prologue + epilogue, in keys
@@ -101,14 +104,16 @@ constexpr int64_t kNarrowKeys = 4 * kAttnKeyTile;
 constexpr int64_t kNarrowIterationKeys = 44;
 constexpr int64_t kNarrowOverheadKeys[2] = {55, 110};
 // The widest items a plan runs narrow: none, those of one row block, or of
-// two.  Ties go to one row block: the tail tile of a longer turn rarely sets
-// the schedule's length, but narrow it takes a third of the time and leaves
-// the rest of the chip its bandwidth and power (256 tokens of 40/8 heads at
-// P=16384, whose sixth tile has 5 rows: 86.5 us against 91.5).  Two have to
-// shorten the schedule (a batch of 16-19 tokens a sequence, one of them
-// narrow for nothing: 39.3 us a layer against 38.2).
+// two.  On a tie none, unless a longer turn's tail tile has one row block: it
+// rarely sets the schedule's length, but narrow it takes a third of the time
+// and leaves the rest of the chip its bandwidth and power (256 tokens of
+// 40/8 heads at P=16384, whose sixth tile has 5 rows: 86.5 us against 91.5).
+// Narrow for nothing costs: a batch of 16-19 tokens a sequence 39.3 us a
+// layer against 38.2, a 16-layer stack of 15 short turns over half-regular
+// caches 907 us against 890.
 constexpr int kNarrowChoices[3] = {0, kAttnNarrowRows / 2, kAttnNarrowRows};
-constexpr int kNarrowOrder[3] = {1, 0, 2};
+constexpr int kNarrowOrder[2][3] = {{0, 1, 2}, {1, 0, 2}};   // [a narrow tail]
+bool narrow_tail(int n_qt, int last_rows) { return n_qt > 1 && last_rows <= kNarrowChoices[1]; }
 
 // Cost of an item in keys of an ordinary workgroup's range.
 int64_t item_cost(int64_t keys, int rows, bool paged, bool split, int narrow_rows) {
@@ -183,7 +188,7 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int 
   int64_t best_chunk = std::max<int64_t>(max_kv, 1), best_span = -1, best_items = 0;
   int best_narrow = 0;
   const int last_rows = n_qt > 0 ? (N - (n_qt - 1) * rows_q) * group : 0;
-  for (int choice : kNarrowOrder) {
+  for (int choice : kNarrowOrder[narrow_tail(n_qt, last_rows)]) {
     if (!narrow_matters(choice, last_rows, rows_q * group, n_qt > 1)) continue;
     const int narrow_rows = kNarrowChoices[choice];
     for (int s = 1; s <= kMaxSplits && n_qt > 0; ++s) {
@@ -206,7 +211,9 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int 
       }
       const int64_t n = (int64_t)nc * hkv;
       const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
-      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
+      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey +
+                                                 (s > kManySplits ? kManySplitsKeys : 0)
+                                           : 0;
       if (best_span >= 0 && span_bound(costs, nc, hkv, slots) + merge + kItemSharedKeys * n > best_span) continue;
       int64_t makespan = *std::max_element(costs, costs + nc);   // one round of workgroups
       if (n > slots) {
@@ -389,7 +396,12 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
   };
   int64_t best_chunk = std::max<int64_t>(max_kv, 1), best_span = -1;
   size_t best_items = 0;
-  for (int choice : kNarrowOrder) {
+  bool tail = false;
+  for (int b = 0; b < batch; ++b) {
+    const int n_qt = (N[b] + rows_q - 1) / rows_q;
+    tail = tail || narrow_tail(n_qt, (N[b] - (n_qt - 1) * rows_q) * group);
+  }
+  for (int choice : kNarrowOrder[tail]) {
     const int narrow_rows = kNarrowChoices[choice];
     bool matters = false;
     for (int b = 0; b < batch && !matters; ++b) {
@@ -417,7 +429,9 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
         const int S = splits_for(chunk, b);
         if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
       }
-      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey : 0;
+      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey +
+                                                 (s > kManySplits ? kManySplitsKeys : 0)
+                                           : 0;
       const int64_t extra = merge + kItemSharedKeys * (int64_t)n;
       if (best_span >= 0 && span_bound(costs.data(), costs.size(), n_kv_heads, slots) + extra > best_span) continue;
       const size_t one = costs.size();
