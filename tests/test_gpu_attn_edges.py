@@ -75,7 +75,7 @@ def test_longest_sequence_head_dim_64():
 
 
 # One query tile per KV head and more than 16 key splits: (P, N, Hq, Hkv).
-MANY_SPLITS = [(4100, 3, 16, 4), (6000, 60, 8, 4), (9001, 17, 40, 8)]
+MANY_SPLITS = [(4100, 50, 8, 2), (16001, 3, 16, 4), (6000, 60, 8, 4), (9001, 17, 40, 8)]
 
 
 @pytest.mark.parametrize("d,dtype", [(64, "bf16"), (64, "f16"), (128, "bf16"), (128, "f16")])
