@@ -55,11 +55,11 @@ ROTATE_BYTES = 512 << 20         # destination buffers the standalone fetch cycl
 # with the hash of the attention source's code (comments left out) they were
 # taken on; a stale entry (the code changed since) is reported as null.
 PMC_TRAFFIC = {
-    "llama3-8b-P8192-N512": (80673560, "b3347e5e53f7ac75"),
-    "llama3-8b-batch16-varlen": (833774953, "b3347e5e53f7ac75"),
-    "qwen-14b-P32768-N1024": (487076777, "b3347e5e53f7ac75"),
-    "llama3-8b-P131072-N2048-hosttier": (1190242354, "b3347e5e53f7ac75"),
-    "llama3-8b-P8192-N512-rc0.5": (79949312, "b3347e5e53f7ac75"),
+    "llama3-8b-P8192-N512": (80621052, "1b022d7d6d184d3a"),
+    "llama3-8b-batch16-varlen": (845016760, "1b022d7d6d184d3a"),
+    "qwen-14b-P32768-N1024": (524601785, "1b022d7d6d184d3a"),
+    "llama3-8b-P131072-N2048-hosttier": (1191092303, "1b022d7d6d184d3a"),
+    "llama3-8b-P8192-N512-rc0.5": (79937222, "1b022d7d6d184d3a"),
 }
 
 

@@ -1044,10 +1044,11 @@ __device__ __forceinline__ void deferred_merge_n(const AttnArgs &a) {
   }
 }
 
+constexpr int kMergeRows = 4;   // rows per lane group, of at most four splits
 template <int D, int DT>
 __device__ __forceinline__ void deferred_merge(const AttnArgs &a) {
   if (a.dm_max_splits <= 4)
-    deferred_merge_n<D, DT, 4, 4>(a);
+    deferred_merge_n<D, DT, kMergeRows, 4>(a);
   else if (a.dm_max_splits <= 16)
     deferred_merge_n<D, DT, 1, 16>(a);
   else
@@ -1118,10 +1119,22 @@ __device__ __forceinline__ void attn_fwd_body(const AttnArgs &a) {
 // kNarrow: for plans with narrow items.  Plans without (every query tile
 // full or nearly so) run the kernel without their body: with it, the 8B-shape
 // stack ran 0.4% slower (a longer start, six more registers).
-template <int D, int DT, bool kNarrow>
+// kBeside: the workgroups from dm_first on do the previous layer's merge, on
+// CUs the items leave idle: after an item, the claims and the rows' round
+// trips ended every layer of a short turn (32-layer stack of a 64-token turn
+// over 1024 tokens: 643 us, 555 beside).  A kernel of its own: the branch in
+// the others cost every call 0.2-0.4 us.
+template <int D, int DT, bool kNarrow, bool kBeside>
 __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnArgs a) {
-  attn_fwd_body<D, DT, kNarrow>(a);
-  if (a.dm_out != nullptr) deferred_merge<D, DT>(a);
+  if constexpr (kBeside) {
+    if ((int)blockIdx.x >= a.dm_first)
+      deferred_merge<D, DT>(a);
+    else
+      attn_fwd_body<D, DT, kNarrow>(a);
+  } else {
+    attn_fwd_body<D, DT, kNarrow>(a);
+    if (a.dm_out != nullptr) deferred_merge<D, DT>(a);
+  }
 }
 
 template <int D, int DT, int SMAX>
@@ -1170,21 +1183,23 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes) {
 
 namespace {
 using FwdKernel = void (*)(AttnArgs);
-FwdKernel fwd_kernel(int head_dim, int dtype, bool narrow) {
-  if (head_dim == 128) {
-    if (dtype == SC_DTYPE_F16)
-      return narrow ? attn_fwd_kernel<128, SC_DTYPE_F16, true> : attn_fwd_kernel<128, SC_DTYPE_F16, false>;
-    return narrow ? attn_fwd_kernel<128, SC_DTYPE_BF16, true> : attn_fwd_kernel<128, SC_DTYPE_BF16, false>;
-  }
-  if (dtype == SC_DTYPE_F16)
-    return narrow ? attn_fwd_kernel<64, SC_DTYPE_F16, true> : attn_fwd_kernel<64, SC_DTYPE_F16, false>;
-  return narrow ? attn_fwd_kernel<64, SC_DTYPE_BF16, true> : attn_fwd_kernel<64, SC_DTYPE_BF16, false>;
+template <bool kNarrow, bool kBeside>
+FwdKernel fwd_kernel_of(int head_dim, int dtype) {
+  if (head_dim == 128)
+    return dtype == SC_DTYPE_F16 ? attn_fwd_kernel<128, SC_DTYPE_F16, kNarrow, kBeside>
+                                 : attn_fwd_kernel<128, SC_DTYPE_BF16, kNarrow, kBeside>;
+  return dtype == SC_DTYPE_F16 ? attn_fwd_kernel<64, SC_DTYPE_F16, kNarrow, kBeside>
+                               : attn_fwd_kernel<64, SC_DTYPE_BF16, kNarrow, kBeside>;
+}
+FwdKernel fwd_kernel(int head_dim, int dtype, bool narrow, bool beside) {
+  if (beside) return narrow ? fwd_kernel_of<true, true>(head_dim, dtype) : fwd_kernel_of<false, true>(head_dim, dtype);
+  return narrow ? fwd_kernel_of<true, false>(head_dim, dtype) : fwd_kernel_of<false, false>(head_dim, dtype);
 }
 }  // namespace
 
-hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_items, hipStream_t stream) {
-  if (n_items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fwd_kernel(head_dim, a.dtype, a.narrow_rows > 0), dim3(n_items), dim3(kThreads), 0, stream, a);
+hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_groups, hipStream_t stream) {
+  if (n_groups <= 0) return hipSuccess;
+  hipLaunchKernelGGL(fwd_kernel(head_dim, a.dtype, a.narrow_rows > 0, a.dm_first > 0), dim3(n_groups), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -1192,26 +1207,32 @@ int attn_fwd_vgprs(int head_dim) {
   // The largest of this head_dim's kernels (element types, item kinds).
   int m = -1;
   for (int dtype : {SC_DTYPE_BF16, SC_DTYPE_F16})
-    for (bool narrow : {false, true}) {
+    for (int kind = 0; kind < 4; ++kind) {
       hipFuncAttributes at{};
-      if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(fwd_kernel(head_dim, dtype, narrow))) != hipSuccess)
-        return -1;
+      const FwdKernel f = fwd_kernel(head_dim, dtype, kind & 1, kind >> 1);
+      if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(f)) != hipSuccess) return -1;
       m = at.numRegs > m ? at.numRegs : m;
     }
   return m;
 }
 
 size_t attn_fwd_lds_bytes(int head_dim, bool narrow) {
-  // The largest static LDS of the two element types' kernels; the full LDS
-  // of a CU if the runtime cannot tell.
+  // The largest static LDS of these kernels; the full LDS of a CU if the
+  // runtime cannot tell.
   size_t m = 0;
-  for (int dtype : {SC_DTYPE_BF16, SC_DTYPE_F16}) {
-    hipFuncAttributes at{};
-    if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(fwd_kernel(head_dim, dtype, narrow))) != hipSuccess)
-      return (size_t)160 << 10;
-    m = at.sharedSizeBytes > m ? at.sharedSizeBytes : m;
-  }
+  for (int dtype : {SC_DTYPE_BF16, SC_DTYPE_F16})
+    for (bool beside : {false, true}) {
+      hipFuncAttributes at{};
+      const FwdKernel f = fwd_kernel(head_dim, dtype, narrow, beside);
+      if (hipFuncGetAttributes(&at, reinterpret_cast<const void *>(f)) != hipSuccess) return (size_t)160 << 10;
+      m = at.sharedSizeBytes > m ? at.sharedSizeBytes : m;
+    }
   return m;
+}
+
+int64_t deferred_merge_chunks(int64_t rows, int head_dim, int max_splits) {
+  const int64_t chunk = (int64_t)(max_splits <= 4 ? kMergeRows : 1) * (kThreads / (head_dim / 8));
+  return (rows + chunk - 1) / chunk;
 }
 
 hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, int max_splits, hipStream_t stream) {

@@ -613,13 +613,15 @@ struct RcView {
 
 // Split-key partials of a layer stack whose merges are deferred: the
 // layer's own partial buffer (ws) and the previous layer's (prev_ws, merged
-// into prev_out by the forward kernel's workgroups before their own items),
+// into prev_out by the forward kernel's workgroups after their own items, or
+// by workgroups without one beside them),
 // both laid out as a plan-sized workspace (partials, then lse).
 struct StackMerge {
   void *ws = nullptr;
   const void *prev_ws = nullptr;
   void *prev_out = nullptr;
   uint32_t *prev_counter = nullptr;   // zero before the launch
+  int slots = 0;                      // attention workgroups the stream's CUs hold at once
 };
 
 
@@ -663,6 +665,7 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
   a.dtype = dtype;
   if (!(scale > 0.f)) scale = 1.f / std::sqrt((float)head_dim);
   a.scale_log2 = scale * 1.4426950408889634f;
+  int n_merge = 0;   // workgroups that only merge
   // Held until the forward and merge kernels are enqueued (see get_workspace).
   std::unique_lock<std::mutex> ws_hold;
   if (plan.max_splits > 1) {
@@ -681,6 +684,15 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
       a.dm_out = static_cast<uint16_t *>(sm->prev_out);
       a.dm_counter = sm->prev_counter;
       a.dm_max_splits = plan.max_splits;
+      // Workgroups for the merge alone on the CUs the items leave idle: one
+      // per chunk of rows, or half as many (two rounds still end before the
+      // items do); with fewer the items' workgroups merge.
+      const int64_t chunks = deferred_merge_chunks((int64_t)plan.total_q * hq, head_dim, plan.max_splits);
+      const int64_t idle = std::min<int64_t>(chunks, (int64_t)sm->slots - plan.n_items);
+      if (idle > 0 && 2 * idle >= chunks) {
+        a.dm_first = plan.n_items;
+        n_merge = (int)idle;
+      }
     }
   }
   if (plan.paged) {
@@ -704,7 +716,7 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
     a.ready_acquire = ready_acquire ? 1 : 0;
   }
   a.done_counter = done_counter;
-  hipError_t e = launch_attn_fwd(a, head_dim, plan.n_items, stream);
+  hipError_t e = launch_attn_fwd(a, head_dim, plan.n_items + n_merge, stream);
   if (e != hipSuccess) return fail_hip(e, "attn_fwd launch");
   if (after_fwd) SC_HIP(hipEventRecord(after_fwd, stream));
   if (plan.max_splits > 1 && !sm) {
@@ -1910,6 +1922,7 @@ sc_status prefill_stack(sc_pool *pool, const sc_table *table, int32_t n_layers, 
   }
   auto stack_merge = [&](int l) {
     StackMerge m;
+    m.slots = ss ? ss->attn_cus * kResidentPerCu : attn_slots(d.device);
     m.ws = dws + (size_t)(l & 1) * dws_half;
     if (l > 0) {
       m.prev_ws = dws + (size_t)((l - 1) & 1) * dws_half;

@@ -196,12 +196,15 @@ struct AttnArgs {
   // part_lse; at most dm_max_splits splits per row) from *dm_counter (zero
   // before the launch) and merges them into dm_out exactly as
   // attn_merge_kernel would, until every chunk is claimed; workgroups that
-  // finish early take more.  dm_out == nullptr: none.
+  // finish early take more.  dm_first > 0: instead, the workgroups from
+  // dm_first on have no item and do all of it, beside the others.
+  // dm_out == nullptr: none.
   const uint16_t *dm_part_o;
   const float *dm_part_lse;
   uint16_t *dm_out;
   uint32_t *dm_counter;
   int32_t dm_max_splits;
+  int32_t dm_first;
 };
 
 // Tile geometry the planner and the kernel agree on.
@@ -223,11 +226,13 @@ constexpr int kAttnMaxSplits = 32; // key splits per sequence (merge kernel boun
 constexpr int kAttnReadySpinLimit = 1 << 22;
 constexpr int kAttnTestSpinLimit = 256;
 
-hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_items, hipStream_t stream);
+hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_groups, hipStream_t stream);
 // Allocation-free calls: the device address of this device's file-scope
 // split-key scratch array (looked up once per device, with that device
 // current) and its size in bytes.
 hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes);
+// Chunks of rows the deferred merge is claimed in.
+int64_t deferred_merge_chunks(int64_t rows, int head_dim, int max_splits);
 size_t attn_fwd_lds_bytes(int head_dim, bool narrow);   // narrow: the kernel for plans with narrow items
 int attn_fwd_vgprs(int head_dim);   // per work item, -1 if unknown
 int kv_copy_vgprs();                // largest of the three copy kernels

@@ -89,16 +89,15 @@ def test_more_than_16_splits(d, dtype):
             _single(sc, p, n, hq, hkv, d, dtype, 7000 + i, noalloc)
 
 
-@pytest.mark.parametrize("d", [64, 128])
-def test_more_than_16_splits_in_a_stack(d):
-    """Merges deferred to the next layer's kernel and the last layer's own."""
+def _stack(seed, p, n, hq, hkv, d):
+    """A three-layer overlapped stack, every layer against the oracle: merges
+    deferred to the next layer's kernel and the last layer's own."""
     sc = require_gpu()
     import torch
     from oracle import kvcache as ok
     from _gpu_util import DevicePool, from_u16, new_active
-    L, hq, hkv = 3, 16, 4
-    wl = W.small_workload(7100, [5000], [21], L, hq, hkv, d)
-    assert sc.sc_attn_plan_query([5000], [21], hq, hkv)[1][0] > 16
+    L = 3
+    wl = W.small_workload(seed, p, n, L, hq, hkv, d)
     pool = W.pool_numpy(wl)
     dp = DevicePool(sc, wl, pool)
     try:
@@ -118,6 +117,28 @@ def test_more_than_16_splits_in_a_stack(d):
             compare_attention(to_u16(outs[l]), ref, f"layer {l}")
     finally:
         dp.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_more_than_16_splits_in_a_stack(d):
+    sc = require_gpu()
+    assert sc.sc_attn_plan_query([5000], [21], 16, 4)[1][0] > 16
+    _stack(7100, [5000], [21], 16, 4, d)
+
+
+# Deferred merges of a layer stack: by workgroups of their own, one chunk of
+# rows each or up to two, or (too few idle CUs) by the items' workgroups; with
+# at most four splits a row and with more.  (P, N, Hq, Hkv, D)
+MERGES = [([378], [10], 10, 2, 64), ([378], [10], 10, 2, 128), ([304], [66], 32, 8, 64), ([304], [66], 32, 8, 128),
+          ([490], [111], 10, 2, 64), ([847], [53], 10, 2, 128), ([616, 323, 694], [150, 71, 110], 32, 8, 128),
+          ([918], [55], 10, 2, 64), ([918], [55], 10, 2, 128), ([807, 1250, 1308], [109, 140, 130], 32, 8, 64)]
+
+
+@pytest.mark.parametrize("i", range(len(MERGES)))
+def test_deferred_merges(i):
+    p, n, hq, hkv, d = MERGES[i]
+    print(f"[merges] P={p} N={n} heads {hq}/{hkv} D={d}", flush=True)
+    _stack(7200 + i, p, n, hq, hkv, d)
 
 
 # Narrow items (at most 64 rows of a query tile): one and two row blocks,
