@@ -135,6 +135,42 @@ bool narrow_matters(int choice, int last_rows, int full_rows, bool has_full) {
   return (last_rows > lo && last_rows <= hi) || (has_full && full_rows > lo && full_rows <= hi);
 }
 
+// What a split choice is made with.
+struct SplitRule {
+  int n_narrow;              // of kNarrowChoices considered
+  int max_splits;
+  int64_t merge_launch_keys;
+};
+constexpr SplitRule kSplitRule = {3, kMaxSplits, kMergeLaunchKeys};
+// Where one sequence's choice needs more partials than the allocation-free
+// entry point's array holds, the choice of ordinary items, at most 16 splits
+// and a merge without its launch gap is taken if it needs less: the rule
+// above may find more splits worth their tail (40/8 heads, P=16384, N=1329:
+// 6 against 1; P=80634, N=909 of 32/8 heads: 11 against 2), and that entry
+// point would refuse a call that fits.  Every entry point takes it, so that
+// their decompositions are the same, and it is priced at head_dim 128 for
+// both head dims.
+constexpr SplitRule kSmallSplitRule = {1, kManySplits, 45};
+struct SplitChoice {
+  int64_t chunk = 1;     // keys per split of the longest sequence
+  int splits = 1;        // of the first sequence
+  int narrow_rows = 0;
+};
+bool partials_fit(int splits, int64_t rows) {
+  return splits == 1 || splits * rows * (int64_t)(128 * sizeof(uint16_t) + sizeof(float)) <= (int64_t)kNoAllocPartialBytes;
+}
+// The choice of one sequence with `rows` (query, head) rows: `choose` makes
+// one by a rule and returns whether it could.
+template <class Fn>
+bool choose_one_sequence(int64_t rows, Fn &&choose, SplitChoice *out) {
+  if (!choose(kSplitRule, out)) return false;
+  if (partials_fit(out->splits, rows)) return true;
+  SplitChoice small;
+  if (!choose(kSmallSplitRule, &small)) return false;
+  if (small.splits < out->splits) *out = small;
+  return true;
+}
+
 struct TileDesc {
   int32_t seq, kvh, q0, nq, keys;
 };
@@ -174,7 +210,7 @@ int64_t lpt_makespan(std::vector<int64_t> &costs, int slots) {
 constexpr int kNoAllocMaxCosts = 4096;
 constexpr int kNoAllocMaxSlots = 2048;
 
-static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out, int *narrow_rows_out) {
+static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, const SplitRule &rule, SplitChoice *out) {
   const int group = hq / hkv;
   const int rows_q = kAttnRows / group;
   const int n_qt = (N + rows_q - 1) / rows_q;
@@ -189,9 +225,9 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int 
   int best_narrow = 0;
   const int last_rows = n_qt > 0 ? (N - (n_qt - 1) * rows_q) * group : 0;
   for (int choice : kNarrowOrder[narrow_tail(n_qt, last_rows)]) {
-    if (!narrow_matters(choice, last_rows, rows_q * group, n_qt > 1)) continue;
+    if (choice >= rule.n_narrow || !narrow_matters(choice, last_rows, rows_q * group, n_qt > 1)) continue;
     const int narrow_rows = kNarrowChoices[choice];
-    for (int s = 1; s <= kMaxSplits && n_qt > 0; ++s) {
+    for (int s = 1; s <= rule.max_splits && n_qt > 0; ++s) {
       int64_t chunk = (max_kv + s - 1) / s;
       chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
       if (s > 1 && chunk < kMinSplitKeys) break;
@@ -211,7 +247,7 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int 
       }
       const int64_t n = (int64_t)nc * hkv;
       const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
-      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey +
+      const int64_t merge = row_splits > 0 ? rule.merge_launch_keys + row_splits / kMergeRowSplitsPerKey +
                                                  (s > kManySplits ? kManySplitsKeys : 0)
                                            : 0;
       if (best_span >= 0 && span_bound(costs, nc, hkv, slots) + merge + kItemSharedKeys * n > best_span) continue;
@@ -237,8 +273,9 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int 
       }
     }
   }
-  *splits_out = splits_of(best_chunk);
-  *narrow_rows_out = last_rows <= best_narrow || rows_q * group <= best_narrow ? best_narrow : 0;
+  out->chunk = best_chunk;
+  out->splits = splits_of(best_chunk);
+  out->narrow_rows = last_rows <= best_narrow || rows_q * group <= best_narrow ? best_narrow : 0;
   return true;
 }
 
@@ -248,7 +285,8 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, int 
 // about 60 us).
 bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits_out, int *narrow_rows_out) {
   struct Choice {
-    int P, N, hq, hkv, slots, splits, narrow_rows;
+    int P, N, hq, hkv, slots;
+    SplitChoice choice;
   };
   constexpr int kChoices = 16;
   static thread_local Choice recent[kChoices] = {};   // hq == 0: empty
@@ -257,13 +295,16 @@ bool single_splits_noalloc(int P, int N, int hq, int hkv, int slots, int *splits
   for (const Choice &x : recent)
     if (x.P == P && x.N == N && x.hq == hq && x.hkv == hkv && x.slots == slots) c = &x;
   if (c == nullptr) {
-    Choice x{P, N, hq, hkv, slots, 1, 0};
-    if (!choose_splits_noalloc(P, N, hq, hkv, slots, &x.splits, &x.narrow_rows)) return false;
+    Choice x{P, N, hq, hkv, slots, {}};
+    if (!choose_one_sequence((int64_t)N * hq, [&](const SplitRule &rule, SplitChoice *out) {
+          return choose_splits_noalloc(P, N, hq, hkv, slots, rule, out);
+        }, &x.choice))
+      return false;
     c = &(recent[next] = x);
     next = (next + 1) % kChoices;
   }
-  *splits_out = c->splits;
-  if (narrow_rows_out) *narrow_rows_out = c->narrow_rows;
+  *splits_out = c->choice.splits;
+  if (narrow_rows_out) *narrow_rows_out = c->choice.narrow_rows;
   return true;
 }
 
@@ -398,58 +439,71 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
     split_counts(chunk, b, &s_rc, &s_sl);
     return s_rc + s_sl;
   };
-  int64_t best_chunk = std::max<int64_t>(max_kv, 1), best_span = -1;
-  size_t best_items = 0;
   bool tail = false;
   for (int b = 0; b < batch; ++b) {
     const int n_qt = (N[b] + rows_q - 1) / rows_q;
     tail = tail || narrow_tail(n_qt, (N[b] - (n_qt - 1) * rows_q) * group);
   }
-  for (int choice : kNarrowOrder[tail]) {
-    const int narrow_rows = kNarrowChoices[choice];
-    bool matters = false;
-    for (int b = 0; b < batch && !matters; ++b) {
-      const int n_qt = (N[b] + rows_q - 1) / rows_q;
-      matters = n_qt > 0 && narrow_matters(choice, (N[b] - (n_qt - 1) * rows_q) * group, rows_q * group, n_qt > 1);
+  auto choose = [&](const SplitRule &rule, SplitChoice *out) {
+    int64_t best_span = -1;
+    size_t best_items = 0;
+    out->chunk = std::max<int64_t>(max_kv, 1);
+    for (int choice : kNarrowOrder[tail]) {
+      if (choice >= rule.n_narrow) continue;
+      const int narrow_rows = kNarrowChoices[choice];
+      bool matters = false;
+      for (int b = 0; b < batch && !matters; ++b) {
+        const int n_qt = (N[b] + rows_q - 1) / rows_q;
+        matters = n_qt > 0 && narrow_matters(choice, (N[b] - (n_qt - 1) * rows_q) * group, rows_q * group, n_qt > 1);
+      }
+      if (!matters) continue;
+      for (int s = 1; s <= rule.max_splits && !tiles.empty(); ++s) {
+        int64_t chunk = (max_kv + s - 1) / s;
+        chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
+        if (s > 1 && chunk < kMinSplitKeys) break;
+        if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
+        std::vector<int64_t> costs;   // of one KV head's items; the others' are the same
+        std::vector<Range> rs;
+        for (const TileDesc &t : tiles) {
+          if (t.kvh != 0) continue;
+          ranges_for(chunk, t.seq, t.keys, &rs);
+          const int S = (int)rs.size();
+          for (const Range &r : rs)
+            costs.push_back(item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, S > 1, narrow_rows));
+        }
+        const size_t n = costs.size() * (size_t)n_kv_heads;
+        int64_t row_splits = 0;
+        for (int b = 0; b < batch; ++b) {
+          const int S = splits_for(chunk, b);
+          if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
+        }
+        const int64_t merge = row_splits > 0 ? rule.merge_launch_keys + row_splits / kMergeRowSplitsPerKey +
+                                                   (s > kManySplits ? kManySplitsKeys : 0)
+                                             : 0;
+        const int64_t extra = merge + kItemSharedKeys * (int64_t)n;
+        if (best_span >= 0 && span_bound(costs.data(), costs.size(), n_kv_heads, slots) + extra > best_span) continue;
+        const size_t one = costs.size();
+        costs.resize(n);
+        for (size_t i = one; i < n; ++i) costs[i] = costs[i - one];
+        const int64_t span = lpt_makespan(costs, slots) + extra;
+        if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
+          best_span = span;
+          best_items = n;
+          out->chunk = chunk;
+          out->narrow_rows = narrow_rows;
+        }
+      }
     }
-    if (!matters) continue;
-    for (int s = 1; s <= kMaxSplits && !tiles.empty(); ++s) {
-      int64_t chunk = (max_kv + s - 1) / s;
-      chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
-      if (s > 1 && chunk < kMinSplitKeys) break;
-      if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
-      std::vector<int64_t> costs;   // of one KV head's items; the others' are the same
-      std::vector<Range> rs;
-      for (const TileDesc &t : tiles) {
-        if (t.kvh != 0) continue;
-        ranges_for(chunk, t.seq, t.keys, &rs);
-        const int S = (int)rs.size();
-        for (const Range &r : rs)
-          costs.push_back(item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, S > 1, narrow_rows));
-      }
-      const size_t n = costs.size() * (size_t)n_kv_heads;
-      int64_t row_splits = 0;
-      for (int b = 0; b < batch; ++b) {
-        const int S = splits_for(chunk, b);
-        if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
-      }
-      const int64_t merge = row_splits > 0 ? kMergeLaunchKeys + row_splits / kMergeRowSplitsPerKey +
-                                                 (s > kManySplits ? kManySplitsKeys : 0)
-                                           : 0;
-      const int64_t extra = merge + kItemSharedKeys * (int64_t)n;
-      if (best_span >= 0 && span_bound(costs.data(), costs.size(), n_kv_heads, slots) + extra > best_span) continue;
-      const size_t one = costs.size();
-      costs.resize(n);
-      for (size_t i = one; i < n; ++i) costs[i] = costs[i - one];
-      const int64_t span = lpt_makespan(costs, slots) + extra;
-      if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
-        best_span = span;
-        best_chunk = chunk;
-        best_items = n;
-        plan->narrow_rows = narrow_rows;
-      }
-    }
-  }
+    out->splits = batch > 0 ? splits_for(out->chunk, 0) : 1;
+    return true;
+  };
+  SplitChoice choice;
+  if (batch == 1 && !plan->paged)
+    choose_one_sequence((int64_t)N[0] * n_q_heads, choose, &choice);
+  else
+    choose(kSplitRule, &choice);
+  const int64_t best_chunk = choice.chunk;
+  plan->narrow_rows = choice.narrow_rows;
   int max_splits = 1;
   for (int b = 0; b < batch; ++b) {
     plan->seqs[b].n_splits = splits_for(best_chunk, b);

@@ -230,6 +230,7 @@ hipError_t launch_attn_fwd(const AttnArgs &a, int head_dim, int n_groups, hipStr
 // Allocation-free calls: the device address of this device's file-scope
 // split-key scratch array (looked up once per device, with that device
 // current) and its size in bytes.
+constexpr size_t kNoAllocPartialBytes = (size_t)64 << 20;
 hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes);
 // Chunks of rows the deferred merge is claimed in.
 int64_t deferred_merge_chunks(int64_t rows, int head_dim, int max_splits);

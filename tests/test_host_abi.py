@@ -2,6 +2,7 @@
 declared symbol; argument validation; the attention work decomposition."""
 
 import ctypes
+import heapq
 import os
 import re
 
@@ -383,6 +384,63 @@ def test_noalloc_split_choice_equals_the_planner(sc):
         for slots in (256, 240, 64):
             _, splits = sc.sc_attn_plan_query([P], [N], hq, hkv, slots)
             assert sc.sc_attn_noalloc_splits(P, N, hq, hkv, slots) == splits[0], (P, N, hq, hkv, slots)
+
+
+def _plain_splits(P, N, hq, hkv, slots):
+    """Key splits by the plainest rule: ordinary items alone, at most 16
+    splits, a schedule of longest items first, a merge without its launch
+    gap (keys of one workgroup's range: 128 per item, 64 more for a split
+    one, 45 and a 600th of the merged rows for the merge, one per item)."""
+    group = hq // hkv
+    rows_q = ROWS // group
+    tiles = [P + min(q0 + rows_q, N) for q0 in range(0, N, rows_q)]
+    best = None
+    for s in range(1, 17):
+        chunk = -(-(-(-(P + N) // s)) // KEY_TILE) * KEY_TILE
+        if s > 1 and chunk < 2 * KEY_TILE:
+            break
+        S = max(1, -(-(P + N) // chunk))
+        costs = []
+        for keys in tiles:
+            t = -(-keys // KEY_TILE)
+            cut = [min(keys, i * t // S * KEY_TILE) for i in range(S + 1)]
+            costs += [b - a + 128 + (64 if S > 1 else 0) for a, b in zip(cut, cut[1:])]
+        n = len(costs) * hkv
+        if n <= slots:
+            span = max(costs)
+        else:
+            heap = [0] * slots
+            for c in sorted(costs, reverse=True):
+                for _ in range(hkv):
+                    heapq.heapreplace(heap, heap[0] + c)
+            span = max(heap)
+        span += n + (45 + N * hq * (S + 1) // 600 if S > 1 else 0)
+        if best is None or (span, n) < best[:2]:
+            best = (span, n, S)
+    return best[2]
+
+
+def test_noalloc_takes_every_call_the_plainest_splits_fit(sc):
+    """The allocation-free entry point refuses a call whose key splits need
+    more partials than its array holds.  Whatever the planner likes better,
+    a call whose plainest splits fit is taken, at either head_dim."""
+    array = 64 << 20
+    shapes = [(16384, 1329, 40, 8), (80634, 909, 32, 8), (50000, 589, 48, 8), (73315, 2956, 8, 2),
+              (65536, 2048, 40, 8), (8192, 512, 32, 8)]
+    for hq, hkv in [(32, 8), (40, 8), (28, 4), (48, 8)]:
+        for P in (0, 500, 8192, 50000, 100000):
+            for N in (24, 256, 512, 777, 909, 1329, 2048):
+                shapes.append((P, N, hq, hkv))
+    rng = np.random.default_rng(2606_16135_74)
+    for _ in range(40):
+        hkv = int(rng.choice([2, 4, 8]))
+        shapes.append((int(rng.integers(0, 100000)), int(rng.integers(1, 3000)), hkv * int(rng.choice([1, 4, 5])), hkv))
+    for P, N, hq, hkv in shapes:
+        plain, splits = _plain_splits(P, N, hq, hkv, 256), sc.sc_attn_noalloc_splits(P, N, hq, hkv, 256)
+        assert sc.sc_attn_plan_query([P], [N], hq, hkv, 256)[1] == [splits]
+        for d in (64, 128):
+            fits = [s == 1 or s * N * hq * (2 * d + 4) <= array for s in (plain, splits)]
+            assert fits[1] or not fits[0], (P, N, hq, hkv, d, plain, splits)
 
 
 def _implicit_items(P, N, hq, hkv, S):

@@ -65,6 +65,30 @@ def test_noalloc_matches_allocating_entry_point_on_successive_calls():
         pytest.fail("expected at least two calls")
 
 
+def test_noalloc_takes_a_call_its_array_would_not_hold_at_more_splits():
+    """Turns whose cheapest schedule has more key splits than the array
+    holds run with fewer, like sc_prefill_attn's."""
+    sc = require_gpu()
+    import torch
+
+    stream = torch.cuda.current_stream().cuda_stream
+    for idx, (P, N, hq, hkv, d) in enumerate([(16384, 1329, 40, 8, 128), (50000, 589, 48, 8, 64)]):
+        print(f"\n[noalloc] P={P} N={N} heads {hq}/{hkv} D={d}", flush=True)
+        q, k, v = _inputs(torch, P, N, hq, hkv, d, 2606_16135_950 + idx)
+        outs = [torch.full((N, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        for f, out in zip((sc.sc_prefill_attn, sc.sc_prefill_attn_noalloc), outs):
+            f(q.data_ptr(), k.data_ptr(), v.data_ptr(), P, N, hq, hkv, d, out.data_ptr(), stream=stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_u16(outs[0]), to_u16(outs[1]))
+        h = hq - 1
+        kf, vf = (oa.bf16_bits_to_f64(to_u16(t[:, hkv - 1:])) for t in (k, v))
+        rows = [(0, i, 0) for i in (0, N // 2, N - 1)]
+        o_ref, _ = oa.attention_rows(oa.bf16_bits_to_f64(to_u16(q[:, h:])), kf, vf, [P], [N], rows)
+        got = to_u16(outs[1])
+        for (_, i, _), ref in zip(rows, o_ref):
+            compare_attention(got[i, h][None, :], ref[None, :], f"row {i}")
+
+
 def test_noalloc_rejects_partials_beyond_its_array():
     """A call whose key splits need more than the array holds is refused
     before any device work (the inputs are real device buffers anyway)."""
