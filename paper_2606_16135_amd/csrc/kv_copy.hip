@@ -188,10 +188,15 @@ hipError_t launch_kv_fill(void *p, size_t bytes, uint16_t pattern, hipStream_t s
 }
 
 int kv_copy_vgprs() {
+  // Every kernel that the copy stream runs between the start of an attention
+  // kernel and the publication of its slot: the copies, the gate that
+  // publishes, the debug poisoning.
   int m = 0;
   for (const void *f : {reinterpret_cast<const void *>(&kv_fetch_kernel), reinterpret_cast<const void *>(&kv_append_kernel),
                         reinterpret_cast<const void *>(&kv_store_kernel),
-                        reinterpret_cast<const void *>(&kv_layer_copy_kernel)}) {
+                        reinterpret_cast<const void *>(&kv_layer_copy_kernel),
+                        reinterpret_cast<const void *>(&slot_gate_kernel),
+                        reinterpret_cast<const void *>(&kv_fill_kernel)}) {
     hipFuncAttributes at{};
     if (hipFuncGetAttributes(&at, f) != hipSuccess) return -1;
     m = at.numRegs > m ? at.numRegs : m;

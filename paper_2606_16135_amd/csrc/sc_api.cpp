@@ -934,9 +934,9 @@ bool dispatch_is_serialised() {
   return serialised;
 }
 
-// Whether a copy workgroup can always start on a CU that holds an attention
-// workgroup (one wave per SIMD beside the attention's two; 512 VGPRs per
-// SIMD lane, allocated in steps of 8).  Only then may attention wait for the
+// Whether a workgroup of any kernel of the copy stream can always start on a
+// CU that holds an attention workgroup (one wave per SIMD beside the
+// attention's two; 512 VGPRs per SIMD lane, allocated in steps of 8).  Only then may attention wait for the
 // copy stream on the device without risking a wait on itself.
 bool copy_fits_beside_attention(int head_dim) {
   const int av = attn_fwd_vgprs(head_dim), cv = kv_copy_vgprs();

@@ -236,7 +236,7 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes);
 int64_t deferred_merge_chunks(int64_t rows, int head_dim, int max_splits);
 size_t attn_fwd_lds_bytes(int head_dim, bool narrow);   // narrow: the kernel for plans with narrow items
 int attn_fwd_vgprs(int head_dim);   // per work item, -1 if unknown
-int kv_copy_vgprs();                // largest of the three copy kernels
+int kv_copy_vgprs();                // largest of the copy stream's kernels, the slot gate's included
 hipError_t launch_attn_merge(const AttnArgs &a, int head_dim, int max_splits, hipStream_t stream);
 
 struct AttnPlan {

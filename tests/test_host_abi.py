@@ -514,6 +514,19 @@ def test_noalloc_argument_validation(sc):
     assert e.value.status == sc.SC_ERR_RANGE
 
 
+def test_register_check_covers_every_kernel_of_the_copy_stream():
+    """An overlapped stack's attention waits on the device for its slot only
+    if every kernel in front of the publication, the publishing gate
+    included, has registers enough to start beside a resident attention
+    workgroup: the check must look at all of them."""
+    src = open(os.path.join(ROOT, "paper_2606_16135_amd", "csrc", "kv_copy.hip")).read()
+    kernels = set(re.findall(r"__global__\s+__launch_bounds__\([^)]*\)\s+void\s+(\w+)\(", src))
+    assert src.count("__global__") == len(kernels) >= 6
+    check = src[src.index("int kv_copy_vgprs() {"):]
+    check = check[:check.index("\n}")]
+    assert kernels == set(re.findall(r"&(\w+)\)", check))
+
+
 def test_noalloc_split_choice_is_the_same_when_asked_again(sc):
     """The allocation-free planner keeps its last choices per thread: more
     shapes than it keeps, asked in two orders and from another thread, give
