@@ -55,11 +55,11 @@ ROTATE_BYTES = 512 << 20         # destination buffers the standalone fetch cycl
 # with the hash of the attention source's code (comments left out) they were
 # taken on; a stale entry (the code changed since) is reported as null.
 PMC_TRAFFIC = {
-    "llama3-8b-P8192-N512": (80621052, "1b022d7d6d184d3a"),
-    "llama3-8b-batch16-varlen": (845016760, "1b022d7d6d184d3a"),
-    "qwen-14b-P32768-N1024": (524601785, "1b022d7d6d184d3a"),
-    "llama3-8b-P131072-N2048-hosttier": (1191092303, "1b022d7d6d184d3a"),
-    "llama3-8b-P8192-N512-rc0.5": (79937222, "1b022d7d6d184d3a"),
+    "llama3-8b-P8192-N512": (80613036, "c0550f556e52ba7d"),
+    "llama3-8b-batch16-varlen": (844585662, "c0550f556e52ba7d"),
+    "qwen-14b-P32768-N1024": (526772008, "c0550f556e52ba7d"),
+    "llama3-8b-P131072-N2048-hosttier": (1190699461, "c0550f556e52ba7d"),
+    "llama3-8b-P8192-N512-rc0.5": (79977569, "c0550f556e52ba7d"),
 }
 
 

@@ -76,6 +76,7 @@
 // address arithmetic per score; against 32-key tiles staged through
 // registers a 32/8-head call of P=8192, N=512 takes 45.2 us instead of 48.0.
 #include "sc_internal.h"
+#include "sc_lds_load.h"
 
 #include <cmath>
 #include <mutex>
@@ -251,20 +252,14 @@ __device__ __forceinline__ void dma_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// One wave's 1 KiB load into LDS at byte address `lds` (in M0 for the
-// instruction, which needs one wait state after the write of M0; nothing
-// else in these kernels uses M0, and saving it cost 0.5-1% of a call).
-// Written out for the kernels with narrow items, whose slots are one array
-// (narrow items pick theirs at run time): around the builtin the compiler
-// would wait for every load in flight before any LDS read.  The waits are
-// dma_barrier's; there is no output register.  Kernels without them keep the
-// builtin and an array per slot: the wait states cost 0.4% of a long loop
-// (131072 keys: 3457 us against 3478).
-__device__ __forceinline__ void load_to_lds(uint32_t lds, int voff, u32x4 rsrc) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(lds), "v"(voff), "s"(rsrc) : "memory");
-}
+// The loads into LDS are written out (load_to_lds) in the kernels with narrow
+// items, whose slots are one array (narrow items pick theirs at run time):
+// around the builtin the compiler would wait for every load in flight before
+// any LDS read.  The waits are dma_barrier's.  Kernels without them keep the
+// builtin and an array per slot: run by the kernel with narrow items, the same
+// plans take 0.5-1.5% longer (32/8 heads, P=131072, N=2048: 3488 us against
+// 3541; 40/8, P=32768, N=1020: 572 against 579; 32/8, P=8192, N=512: 68.8
+// against 69.4; head_dim 64, P=32768, N=1024: 274.7 against 276.2).
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
 }
@@ -600,17 +595,14 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(slot + my_lds), 16,
                                                kV ? voff_v : voff_k[0], 0, 0, 0);
     } else {
-      // The resource's second word holds address bits 32-47 and, above them,
-      // a stride of zero: the address as it is (device addresses have 48
-      // bits).
       const uint64_t ad = reinterpret_cast<uint64_t>(base);
-      const u32x4 rs = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ad),
-                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ad >> 32)),
-                        (uint32_t)__builtin_amdgcn_readfirstlane(range), 0x00020000u};
+      const uint64_t from = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ad >> 32)) << 32 |
+                            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ad);
       const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_address(slot) + my_lds + (kV ? kV0 : 0)));
+      int voff[KG];
 #pragma unroll
-      for (int i = 0; i < KG; ++i)
-        load_to_lds(to + 1024 * i, kV ? voff_v + i * G_::kRowsPerLoad * row_bytes : voff_k[i], rs);
+      for (int i = 0; i < KG; ++i) voff[i] = kV ? voff_v + i * G_::kRowsPerLoad * row_bytes : voff_k[i];
+      load_to_lds(to, voff, from, (uint32_t)__builtin_amdgcn_readfirstlane(range));
     }
   };
   auto qk = [&](const unsigned char *slot, f32x16 (&s)[NB]) {
@@ -1151,8 +1143,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // Split-key partials of the allocation-free entry point: one array per
 // device, held by the loaded code object until the process ends.  Host code
 // must use the address hipGetSymbolAddress returns, never the symbol.
-constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocPartialBytes];
 
 }  // namespace
 
@@ -1177,7 +1168,7 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes) {
     addr[device] = p;
   }
   *ptr = addr[device];
-  *bytes = kNoAllocScratchBytes;
+  *bytes = kNoAllocPartialBytes;
   return hipSuccess;
 }
 
