@@ -287,6 +287,12 @@ sc_status sc_prefill_attn_noalloc(const void *q, const void *k_active, const voi
 sc_status sc_attn_noalloc_splits(int32_t prefix_len, int32_t new_len, int32_t n_q_heads,
                                  int32_t n_kv_heads, int32_t slots, int32_t *splits);
 
+/* Host only: the rows up to which sc_prefill_attn_noalloc runs an item
+ * narrow, which equals sc_attn_plan_kinds's for the same sequence.
+ * Arguments and errors as sc_attn_noalloc_splits. */
+sc_status sc_attn_noalloc_narrow_rows(int32_t prefix_len, int32_t new_len, int32_t n_q_heads,
+                                      int32_t n_kv_heads, int32_t slots, int32_t *narrow_rows);
+
 /* The same attention for every sequence of a table (packed varlen layout)
  * at layer `layer`: q, out [sum N][n_q_heads][head_dim]; kv = the active
  * buffer filled by sc_fetch_layer_kv + sc_append_new_kv; lse (nullable)
@@ -335,7 +341,8 @@ sc_status sc_store_layer_kv(sc_pool *pool, const sc_table *table, int32_t layer,
  * threads or caller streams (each starts after the previous one ended).
  * When the attention plan splits key ranges, layer l's split partials are
  * merged by the forward kernel of layer l+1 (its workgroups take chunks of
- * rows once their own work items are done) and the last layer's by one
+ * rows once their own work items are done, or, where the items leave CUs
+ * idle, workgroups without an item do) and the last layer's by one
  * merge kernel; out_per_layer[l] is therefore complete only when the whole
  * stack is, which is when the compute stream reaches the end of the stack.
  * The partials use the library's split-key workspace of the attention
@@ -430,6 +437,20 @@ sc_status sc_prefill_stack_chunked(sc_pool *pool, const sc_table *table, int32_t
 sc_status sc_attn_plan_query(int32_t batch, const int32_t *prefix_len, const int32_t *new_len,
                              const int32_t *rc_keys, int32_t n_q_heads, int32_t n_kv_heads, int32_t slots,
                              int32_t *n_items, int32_t *items, int32_t capacity, int32_t *splits);
+
+/*
+ * Host-only, of the same plan: which kernels run it.  *narrow_rows: items of
+ * at most this many rows (n_queries x the group's heads) outside the regular
+ * cache are narrow, i.e. their workgroup spreads its waves over four groups
+ * of keys instead of 256 rows; 0 when the plan has none.  *merge_groups: the
+ * workgroups that a layer stack's attention launch adds for the merge of the
+ * previous layer's key splits, on CUs the items leave idle; 0 when the items'
+ * workgroups merge after their items, or nothing is split.
+ * Errors: as sc_attn_plan_query, plus SC_ERR_UNSUPPORTED (head_dim).
+ */
+sc_status sc_attn_plan_kinds(int32_t batch, const int32_t *prefix_len, const int32_t *new_len,
+                             const int32_t *rc_keys, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                             int32_t slots, int32_t *narrow_rows, int32_t *merge_groups);
 
 /* ------------------------------------------------------------------------
  * Elastic donor tier and capacity planning (host only, no device work).

@@ -686,6 +686,17 @@ size_t plan_ws_bytes(const AttnPlan &plan, int hq, int head_dim, size_t *lse_off
   return rows * ((size_t)head_dim * sizeof(uint16_t) + sizeof(float));
 }
 
+// Workgroups a layer stack's launch of this plan adds for the merge of the
+// previous layer's partials, on the CUs that the items leave idle: one per
+// chunk of rows, or half as many (two rounds still end before the items do);
+// with fewer than that none, and the items' workgroups merge.
+int beside_merge_groups(const AttnPlan &plan, int hq, int head_dim, int slots) {
+  if (plan.max_splits <= 1) return 0;
+  const int64_t chunks = deferred_merge_chunks((int64_t)plan.total_q * hq, head_dim, plan.max_splits);
+  const int64_t idle = std::min<int64_t>(chunks, (int64_t)slots - plan.n_items);
+  return idle > 0 && 2 * idle >= chunks ? (int)idle : 0;
+}
+
 sc_status run_attention(int device, const AttnPlan &plan, const void *q, const void *k, const void *v,
                         void *out, float *lse, int hq, int hkv, int head_dim, int dtype, float scale,
                         hipStream_t stream, const uint64_t *ready_flag = nullptr, uint64_t ready_value = 0,
@@ -738,15 +749,8 @@ sc_status run_attention(int device, const AttnPlan &plan, const void *q, const v
       a.dm_out = static_cast<uint16_t *>(sm->prev_out);
       a.dm_counter = sm->prev_counter;
       a.dm_max_splits = plan.max_splits;
-      // Workgroups for the merge alone on the CUs the items leave idle: one
-      // per chunk of rows, or half as many (two rounds still end before the
-      // items do); with fewer the items' workgroups merge.
-      const int64_t chunks = deferred_merge_chunks((int64_t)plan.total_q * hq, head_dim, plan.max_splits);
-      const int64_t idle = std::min<int64_t>(chunks, (int64_t)sm->slots - plan.n_items);
-      if (idle > 0 && 2 * idle >= chunks) {
-        a.dm_first = plan.n_items;
-        n_merge = (int)idle;
-      }
+      n_merge = beside_merge_groups(plan, hq, head_dim, sm->slots);
+      if (n_merge > 0) a.dm_first = plan.n_items;
     }
   }
   if (plan.paged) {
@@ -1090,6 +1094,30 @@ LayerCopyArgs layer_copy_args(const sc_pool *p, const sc_table *t, int layer, co
   }
   if (!store) la.part[2].n_items = 0;
   return la;
+}
+
+// The host-only plan queries' checks and plan.
+sc_status check_plan_query(int32_t batch, const int32_t *prefix_len, const int32_t *new_len, const int32_t *rc_keys,
+                           int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim) {
+  if (batch <= 0 || !prefix_len || !new_len) return fail(SC_ERR_INVALID, "null argument");
+  sc_status st = check_heads(n_q_heads, n_kv_heads, head_dim);
+  if (st != SC_OK) return st;
+  for (int b = 0; b < batch; ++b) {
+    if (prefix_len[b] < 0 || new_len[b] < 0) return fail(SC_ERR_INVALID, "negative length");
+    if (rc_keys && (rc_keys[b] < 0 || rc_keys[b] > prefix_len[b]))
+      return fail(SC_ERR_INVALID, "sequence %d: regular-cache keys %d outside [0, %d]", b, rc_keys[b],
+                  prefix_len[b]);
+  }
+  return SC_OK;
+}
+
+void plan_query(int32_t batch, const int32_t *prefix_len, const int32_t *new_len, const int32_t *rc_keys,
+                int32_t n_q_heads, int32_t n_kv_heads, int32_t slots, AttnPlan *plan) {
+  std::vector<int32_t> rc;
+  if (rc_keys) rc.assign(rc_keys, rc_keys + batch);
+  plan_attention(std::vector<int32_t>(prefix_len, prefix_len + batch),
+                 std::vector<int32_t>(new_len, new_len + batch), n_q_heads, n_kv_heads,
+                 slots > 0 ? slots : kQueryDefaultSlots, plan, rc, std::vector<int32_t>(rc.size(), 0));
 }
 
 sc_status prefill_attn_single(const void *q, const void *k_active, const void *v_active, int32_t prefix_len,
@@ -1598,21 +1626,11 @@ sc_status sc_attn_plan_query(int32_t batch, const int32_t *prefix_len, const int
                              const int32_t *rc_keys, int32_t n_q_heads, int32_t n_kv_heads, int32_t slots,
                              int32_t *n_items, int32_t *items, int32_t capacity, int32_t *splits) {
   clear_error();
-  if (batch <= 0 || !prefix_len || !new_len || !n_items) return fail(SC_ERR_INVALID, "null argument");
-  sc_status st = check_heads(n_q_heads, n_kv_heads, 128);
+  if (!n_items) return fail(SC_ERR_INVALID, "null argument");
+  sc_status st = check_plan_query(batch, prefix_len, new_len, rc_keys, n_q_heads, n_kv_heads, 128);
   if (st != SC_OK) return st;
-  for (int b = 0; b < batch; ++b) {
-    if (prefix_len[b] < 0 || new_len[b] < 0) return fail(SC_ERR_INVALID, "negative length");
-    if (rc_keys && (rc_keys[b] < 0 || rc_keys[b] > prefix_len[b]))
-      return fail(SC_ERR_INVALID, "sequence %d: regular-cache keys %d outside [0, %d]", b, rc_keys[b],
-                  prefix_len[b]);
-  }
-  std::vector<int32_t> rc;
-  if (rc_keys) rc.assign(rc_keys, rc_keys + batch);
   AttnPlan plan;
-  plan_attention(std::vector<int32_t>(prefix_len, prefix_len + batch),
-                 std::vector<int32_t>(new_len, new_len + batch), n_q_heads, n_kv_heads,
-                 slots > 0 ? slots : kQueryDefaultSlots, &plan, rc, std::vector<int32_t>(rc.size(), 0));
+  plan_query(batch, prefix_len, new_len, rc_keys, n_q_heads, n_kv_heads, slots, &plan);
   *n_items = plan.n_items;
   if (items) {
     if (capacity < plan.n_items) return fail(SC_ERR_RANGE, "capacity %d < %d items", capacity, plan.n_items);
@@ -1620,6 +1638,20 @@ sc_status sc_attn_plan_query(int32_t batch, const int32_t *prefix_len, const int
   }
   if (splits)
     for (int b = 0; b < batch; ++b) splits[b] = plan.seqs[b].n_splits;
+  return SC_OK;
+}
+
+sc_status sc_attn_plan_kinds(int32_t batch, const int32_t *prefix_len, const int32_t *new_len,
+                             const int32_t *rc_keys, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                             int32_t slots, int32_t *narrow_rows, int32_t *merge_groups) {
+  clear_error();
+  if (!narrow_rows || !merge_groups) return fail(SC_ERR_INVALID, "null argument");
+  sc_status st = check_plan_query(batch, prefix_len, new_len, rc_keys, n_q_heads, n_kv_heads, head_dim);
+  if (st != SC_OK) return st;
+  AttnPlan plan;
+  plan_query(batch, prefix_len, new_len, rc_keys, n_q_heads, n_kv_heads, slots, &plan);
+  *narrow_rows = plan.narrow_rows;
+  *merge_groups = beside_merge_groups(plan, n_q_heads, head_dim, slots > 0 ? slots : kQueryDefaultSlots);
   return SC_OK;
 }
 
@@ -1849,6 +1881,20 @@ sc_status sc_attn_noalloc_splits(int32_t prefix_len, int32_t new_len, int32_t n_
                              &S, nullptr))
     return fail(SC_ERR_RANGE, "shape exceeds the allocation-free planner's buffers");
   *splits = S;
+  return SC_OK;
+}
+
+sc_status sc_attn_noalloc_narrow_rows(int32_t prefix_len, int32_t new_len, int32_t n_q_heads, int32_t n_kv_heads,
+                                      int32_t slots, int32_t *narrow_rows) {
+  clear_error();
+  if (!narrow_rows) return fail(SC_ERR_INVALID, "null argument");
+  if (prefix_len < 0 || new_len < 0) return fail(SC_ERR_INVALID, "negative length");
+  sc_status st = check_heads(n_q_heads, n_kv_heads, 128);
+  if (st != SC_OK) return st;
+  int S = 1;
+  if (!single_splits_noalloc(prefix_len, new_len, n_q_heads, n_kv_heads, slots > 0 ? slots : kQueryDefaultSlots,
+                             &S, narrow_rows))
+    return fail(SC_ERR_RANGE, "shape exceeds the allocation-free planner's buffers");
   return SC_OK;
 }
 

@@ -44,6 +44,7 @@ EXPORTED = [
     "sc_table_destroy", "sc_table_totals", "sc_table_stack_status", "sc_stack_wait_kind", "sc_fetch_layer_kv",
     "sc_fetch_layer_kv_dma", "sc_append_new_kv",
     "sc_prefill_attn", "sc_prefill_attn_f16", "sc_prefill_attn_noalloc", "sc_attn_noalloc_splits",
+    "sc_attn_noalloc_narrow_rows", "sc_attn_plan_kinds",
     "sc_prefill_attn_varlen", "sc_store_layer_kv",
     "sc_prefill_stack", "sc_prefill_stack_chunked", "sc_attn_plan_query", "sc_pool_resize", "sc_plan_capacity", "sc_elastic_unit", "sc_scale_up",
     "sc_scale_down", "sc_last_error", "sc_version",
@@ -121,6 +122,8 @@ def load():
         "sc_prefill_attn_f16": (I32, [VP, VP, VP, I32, I32, I32, I32, I32, F32, VP, VP, VP]),
         "sc_prefill_attn_noalloc": (I32, [VP, VP, VP, I32, I32, I32, I32, I32, F32, VP, VP, VP]),
         "sc_attn_noalloc_splits": (I32, [I32, I32, I32, I32, I32, i32p]),
+        "sc_attn_noalloc_narrow_rows": (I32, [I32, I32, I32, I32, I32, i32p]),
+        "sc_attn_plan_kinds": (I32, [I32, i32p, i32p, VP, I32, I32, I32, I32, i32p, i32p]),
         "sc_prefill_attn_varlen": (I32, [P, P, I32, VP, ctypes.POINTER(sc_active), I32, F32, VP, VP, VP]),
         "sc_store_layer_kv": (I32, [P, P, I32, VP, VP, VP]),
         "sc_prefill_stack": (I32, [P, P, I32, ctypes.POINTER(VP), ctypes.POINTER(VP),
@@ -260,6 +263,22 @@ def sc_attn_noalloc_splits(prefix_len, new_len, n_q_heads, n_kv_heads, slots=0):
     s = ctypes.c_int32()
     _check(load().sc_attn_noalloc_splits(prefix_len, new_len, n_q_heads, n_kv_heads, slots, ctypes.byref(s)))
     return s.value
+
+
+def sc_attn_noalloc_narrow_rows(prefix_len, new_len, n_q_heads, n_kv_heads, slots=0):
+    r = ctypes.c_int32()
+    _check(load().sc_attn_noalloc_narrow_rows(prefix_len, new_len, n_q_heads, n_kv_heads, slots, ctypes.byref(r)))
+    return r.value
+
+
+def sc_attn_plan_kinds(prefix_len, new_len, n_q_heads, n_kv_heads, head_dim=128, slots=0, rc_keys=None):
+    """Returns (narrow_rows, merge_groups)."""
+    narrow, merge = ctypes.c_int32(), ctypes.c_int32()
+    rc_arr = _i32_array(rc_keys) if rc_keys is not None else None
+    rc = ctypes.cast(rc_arr, ctypes.c_void_p) if rc_arr is not None else None
+    _check(load().sc_attn_plan_kinds(len(prefix_len), _i32_array(prefix_len), _i32_array(new_len), rc, n_q_heads,
+                                     n_kv_heads, head_dim, slots, ctypes.byref(narrow), ctypes.byref(merge)))
+    return narrow.value, merge.value
 
 
 def sc_prefill_attn_varlen(pool, table, layer, q, kv, n_q_heads, out, lse=0, scale=0.0, stream=0):

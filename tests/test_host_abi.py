@@ -386,6 +386,40 @@ def test_noalloc_split_choice_equals_the_planner(sc):
             assert sc.sc_attn_noalloc_splits(P, N, hq, hkv, slots) == splits[0], (P, N, hq, hkv, slots)
 
 
+def test_noalloc_runs_the_same_items_narrow(sc):
+    """... and run the same items narrow, for the same reason."""
+    rng = np.random.default_rng(2606_16135_73)
+    shapes = [(500, 1, 8, 2), (500, 8, 8, 2), (4000, 16, 8, 2), (16384, 256, 40, 8), (32768, 1024, 40, 8),
+              (8192, 512, 32, 8), (256, 64, 8, 8)]
+    for _ in range(200):
+        hkv = int(rng.choice([1, 2, 4, 8]))
+        g = int(rng.choice([1, 3, 4, 5, 7, 16]))
+        p, n = (int(np.exp(rng.uniform(0, top))) for top in (10.5, 7.0))
+        shapes.append((p, n, hkv * g, hkv))
+    kinds = set()
+    for P, N, hq, hkv in shapes:
+        for slots in (256, 240):
+            narrow, _ = sc.sc_attn_plan_kinds([P], [N], hq, hkv, 128, slots)
+            assert sc.sc_attn_noalloc_narrow_rows(P, N, hq, hkv, slots) == narrow, (P, N, hq, hkv, slots)
+            kinds.add(narrow)
+    assert kinds == {0, 32, 64}
+
+
+def test_plan_kinds_validation(sc):
+    with pytest.raises(sc.SwiftCacheError) as e:
+        sc.sc_attn_plan_kinds([100], [10], 8, 8, 96)
+    assert e.value.status == sc.SC_ERR_UNSUPPORTED
+    with pytest.raises(sc.SwiftCacheError) as e:
+        sc.sc_attn_plan_kinds([100], [10], 8, 8, rc_keys=[112])
+    assert e.value.status == sc.SC_ERR_INVALID
+    with pytest.raises(sc.SwiftCacheError) as e:
+        sc.sc_attn_noalloc_narrow_rows(-1, 10, 8, 8)
+    assert e.value.status == sc.SC_ERR_INVALID
+    # 64 tokens of 32/8 heads over 1024: 8 tiles leave CUs for the merges.
+    assert sc.sc_attn_plan_kinds([1024], [64], 32, 8, 128)[1] > 0
+    assert sc.sc_attn_plan_kinds([8192], [512], 32, 8, 128)[1] == 0
+
+
 def _plain_splits(P, N, hq, hkv, slots):
     """Key splits by the plainest rule: ordinary items alone, at most 16
     splits, a schedule of longest items first, a merge without its launch
