@@ -186,27 +186,114 @@ int64_t span_bound(const int64_t *costs, size_t n, int64_t copies, int slots) {
   return std::max(top, (sum * copies + slots - 1) / std::max(1, slots));
 }
 
-// Longest-processing-time schedule of `costs` on `slots` identical slots.
-int64_t lpt_makespan(std::vector<int64_t> &costs, int slots) {
-  if (!costs.empty() && costs.size() <= (size_t)std::max(1, slots)) return *std::max_element(costs.begin(), costs.end());
-  std::sort(costs.begin(), costs.end(), std::greater<int64_t>());
-  std::vector<int64_t> heap(std::max(1, slots), 0);   // min-heap of slot loads
+// Scratch of a split search: item costs of one KV head, and loads of slots.
+struct SplitScratch {
+  int64_t *costs;
+  int64_t *busy;       // busy_slots(slots) entries
+};
+constexpr int kShaderEngines = 4;   // per XCD
+int busy_slots(int slots) { return std::max(1, slots) + kXcds * kShaderEngines; }
+
+// Longest-processing-time schedule on `slots` identical slots of n costs in
+// descending order, each `copies` times.
+int64_t lpt_makespan(const int64_t *costs, size_t n, int copies, int slots, int64_t *busy) {
+  if (n * copies <= (size_t)slots) return costs[0];
+  std::fill(busy, busy + slots, (int64_t)0);   // all zero: already a heap
   auto cmp = std::greater<int64_t>();
-  std::make_heap(heap.begin(), heap.end(), cmp);
-  for (int64_t c : costs) {
-    std::pop_heap(heap.begin(), heap.end(), cmp);
-    heap.back() += c;
-    std::push_heap(heap.begin(), heap.end(), cmp);
+  for (size_t i = 0; i < n; ++i)
+    for (int g = 0; g < copies; ++g) {
+      std::pop_heap(busy, busy + slots, cmp);
+      busy[slots - 1] += costs[i];
+      std::push_heap(busy, busy + slots, cmp);
+    }
+  return *std::max_element(busy, busy + slots);
+}
+
+// Time one XCD takes for n items in the order given: its dispatcher hands
+// workgroups to its shader engines in turn and does not pass over one whose
+// CUs are all busy.  So a few short items behind long ones do not fit into
+// the CUs left over unless every engine has some: 30 long items and 5 short
+// ones on the 32 CUs of an XCD end after a long and a short one's time (280
+// items at P=60000, N=392 of 32/8 heads: 416 us, and 366 as 224 ordinary
+// ones), 24 and 12 with the long ones' (288 items at P=16384, N=107 of 40/8
+// heads: 44.8 us, 49.8 as 240 ordinary ones).
+template <class Cost>
+int64_t dispatch_span(int64_t n, int xcd_slots, int64_t *busy, Cost &&cost) {
+  int64_t *at[kShaderEngines + 1] = {busy};
+  for (int e = 0; e < kShaderEngines; ++e)
+    at[e + 1] = at[e] + std::max(1, (xcd_slots + kShaderEngines - 1 - e) / kShaderEngines);
+  std::fill(busy, at[kShaderEngines], (int64_t)0);
+  auto cmp = std::greater<int64_t>();
+  int64_t now = 0, end = 0;
+  for (int64_t i = 0; i < n; ++i) {
+    int64_t *const b = at[i % kShaderEngines], *const e = at[i % kShaderEngines + 1];
+    now = std::max(now, *b);
+    std::pop_heap(b, e, cmp);
+    e[-1] = now + cost(i);
+    end = std::max(end, e[-1]);
+    std::push_heap(b, e, cmp);
   }
-  return *std::max_element(heap.begin(), heap.end());
+  return end;
+}
+
+// The splits of a plan: every sequence is cut into chunks of at most `chunk`
+// keys; try the chunk sizes that give 1, 2, .. splits to the longest sequence
+// (max_kv keys), with the items of each kind that matters run narrow, and
+// keep the shortest schedule.  Ordinary items run in the order of their
+// costs; where some are narrow they are placed in that order too if that ends
+// earlier (place_items), and a schedule of several rounds is what the
+// dispatchers make of it.  n_tiles: query tiles of all KV heads; costs_of:
+// writes the items' costs of one KV head for a chunk size and returns their
+// number, negative if they do not fit; row_splits: merged (row, split) pairs.
+template <class CostsFn, class RowsFn>
+bool choose_splits(const SplitRule &rule, int64_t max_kv, int64_t n_tiles, int hkv, int slots, bool tail,
+                   const bool (&matters)[3], const SplitScratch &scratch, CostsFn &&costs_of, RowsFn &&row_splits,
+                   SplitChoice *out) {
+  int64_t best_span = -1, best_items = 0;
+  out->chunk = std::max<int64_t>(max_kv, 1);
+  out->narrow_rows = 0;
+  if (n_tiles == 0) return true;
+  for (int choice : kNarrowOrder[tail]) {
+    if (choice >= rule.n_narrow || !matters[choice]) continue;
+    const int narrow_rows = kNarrowChoices[choice];
+    for (int s = 1; s <= rule.max_splits; ++s) {
+      int64_t chunk = (max_kv + s - 1) / s;
+      chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
+      if (s > 1 && chunk < kMinSplitKeys) break;
+      if (s > kManySplits && n_tiles * s > slots) break;
+      int64_t *const costs = scratch.costs;
+      const int64_t one = costs_of(chunk, narrow_rows, costs);
+      if (one < 0) return false;
+      const int64_t n = one * hkv, rows = row_splits(chunk);
+      const int64_t extra = kItemSharedKeys * n +
+                            (rows > 0 ? rule.merge_launch_keys + rows / kMergeRowSplitsPerKey +
+                                            (s > kManySplits ? kManySplitsKeys : 0)
+                                      : 0);
+      if (best_span >= 0 && span_bound(costs, one, hkv, slots) + extra > best_span) continue;
+      std::sort(costs, costs + one, std::greater<int64_t>());
+      int64_t span = 0;
+      if (choice == 0 || n <= slots)
+        span = lpt_makespan(costs, one, hkv, slots, scratch.busy);
+      else
+        for (int x = 0; x < kXcds; ++x)
+          span = std::max(span, dispatch_span((n - x + kXcds - 1) / kXcds, slots / kXcds, scratch.busy,
+                                              [&](int64_t i) { return costs[(i * kXcds + x) / hkv]; }));
+      span += extra;
+      if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
+        best_span = span;
+        best_items = n;
+        out->chunk = chunk;
+        out->narrow_rows = narrow_rows;
+      }
+    }
+  }
+  return true;
 }
 }  // namespace
 
-// The split count plan_attention chooses for one sequence without a
-// regular cache, computed in fixed-size buffers (no heap memory): the same
-// candidates, item costs, LPT schedule and merge term.  Each (query tile,
-// split) cost stands for n_kv_heads identical items.  Returns false when the
-// candidates' item lists exceed the buffers.
+// The choice plan_attention makes for one sequence without a regular cache,
+// in fixed-size buffers (no heap memory).  Returns false when the candidates'
+// item lists exceed the buffers.
 constexpr int kNoAllocMaxCosts = 4096;
 constexpr int kNoAllocMaxSlots = 2048;
 
@@ -217,65 +304,38 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, cons
   const int64_t max_kv = (int64_t)P + N;
   if (slots < 1 || slots > kNoAllocMaxSlots) return false;
   int64_t costs[kNoAllocMaxCosts];
-  int64_t heap[kNoAllocMaxSlots];
+  int64_t busy[kNoAllocMaxSlots + kXcds * kShaderEngines];
   auto splits_of = [&](int64_t chunk) {
     return (int)std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, (max_kv + chunk - 1) / chunk));
   };
-  int64_t best_chunk = std::max<int64_t>(max_kv, 1), best_span = -1, best_items = 0;
-  int best_narrow = 0;
   const int last_rows = n_qt > 0 ? (N - (n_qt - 1) * rows_q) * group : 0;
-  for (int choice : kNarrowOrder[narrow_tail(n_qt, last_rows)]) {
-    if (choice >= rule.n_narrow || !narrow_matters(choice, last_rows, rows_q * group, n_qt > 1)) continue;
-    const int narrow_rows = kNarrowChoices[choice];
-    for (int s = 1; s <= rule.max_splits && n_qt > 0; ++s) {
-      int64_t chunk = (max_kv + s - 1) / s;
-      chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
-      if (s > 1 && chunk < kMinSplitKeys) break;
-      if (s > kManySplits && (int64_t)n_qt * hkv * s > slots) break;
-      const int S = splits_of(chunk);
-      if ((int64_t)n_qt * S > kNoAllocMaxCosts) return false;
-      int nc = 0;
-      for (int tile = 0; tile < n_qt; ++tile) {
-        const int q0 = tile * rows_q;
-        const int keys = P + q0 + std::min(rows_q, N - q0);
-        const int t = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
-        for (int sp = 0; sp < S; ++sp) {
-          const int b0 = std::min(keys, (int)((int64_t)sp * t / S) * kAttnKeyTile);
-          const int b1 = std::min(keys, (int)((int64_t)(sp + 1) * t / S) * kAttnKeyTile);
-          costs[nc++] = item_cost(std::max(b0, b1) - b0, std::min(rows_q, N - q0) * group, false, S > 1, narrow_rows);
-        }
-      }
-      const int64_t n = (int64_t)nc * hkv;
-      const int64_t row_splits = S > 1 ? (int64_t)N * hq * (S + 1) : 0;
-      const int64_t merge = row_splits > 0 ? rule.merge_launch_keys + row_splits / kMergeRowSplitsPerKey +
-                                                 (s > kManySplits ? kManySplitsKeys : 0)
-                                           : 0;
-      if (best_span >= 0 && span_bound(costs, nc, hkv, slots) + merge + kItemSharedKeys * n > best_span) continue;
-      int64_t makespan = *std::max_element(costs, costs + nc);   // one round of workgroups
-      if (n > slots) {
-        std::sort(costs, costs + nc, std::greater<int64_t>());
-        std::fill(heap, heap + slots, (int64_t)0);   // all zero: already a heap
-        auto cmp = std::greater<int64_t>();
-        for (int i = 0; i < nc; ++i)
-          for (int g = 0; g < hkv; ++g) {
-            std::pop_heap(heap, heap + slots, cmp);
-            heap[slots - 1] += costs[i];
-            std::push_heap(heap, heap + slots, cmp);
-          }
-        makespan = *std::max_element(heap, heap + slots);
-      }
-      const int64_t span = makespan + merge + kItemSharedKeys * n;
-      if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
-        best_span = span;
-        best_chunk = chunk;
-        best_items = n;
-        best_narrow = narrow_rows;
+  bool matters[3];
+  for (int c = 0; c < 3; ++c) matters[c] = narrow_matters(c, last_rows, rows_q * group, n_qt > 1);
+  auto costs_of = [&](int64_t chunk, int narrow_rows, int64_t *to) -> int64_t {
+    const int S = splits_of(chunk);
+    if ((int64_t)n_qt * S > kNoAllocMaxCosts) return -1;
+    int64_t n = 0;
+    for (int tile = 0; tile < n_qt; ++tile) {
+      const int q0 = tile * rows_q;
+      const int keys = P + q0 + std::min(rows_q, N - q0);
+      const int t = (keys + kAttnKeyTile - 1) / kAttnKeyTile;
+      for (int sp = 0; sp < S; ++sp) {
+        const int b0 = std::min(keys, (int)((int64_t)sp * t / S) * kAttnKeyTile);
+        const int b1 = std::min(keys, (int)((int64_t)(sp + 1) * t / S) * kAttnKeyTile);
+        to[n++] = item_cost(std::max(b0, b1) - b0, std::min(rows_q, N - q0) * group, false, S > 1, narrow_rows);
       }
     }
-  }
-  out->chunk = best_chunk;
-  out->splits = splits_of(best_chunk);
-  out->narrow_rows = last_rows <= best_narrow || rows_q * group <= best_narrow ? best_narrow : 0;
+    return n;
+  };
+  auto row_splits = [&](int64_t chunk) {
+    const int S = splits_of(chunk);
+    return S > 1 ? (int64_t)N * hq * (S + 1) : 0;
+  };
+  if (!choose_splits(rule, max_kv, (int64_t)n_qt * hkv, hkv, slots, narrow_tail(n_qt, last_rows), matters,
+                     SplitScratch{costs, busy}, costs_of, row_splits, out))
+    return false;
+  out->splits = splits_of(out->chunk);
+  if (!(last_rows <= out->narrow_rows || rows_q * group <= out->narrow_rows)) out->narrow_rows = 0;
   return true;
 }
 
@@ -330,7 +390,7 @@ struct GroupItems {
 // Places the items of each (sequence, KV head) group on one XCD (workgroup
 // w runs on XCD w mod 8), groups by decreasing cost onto the least loaded
 // XCD, longest items first within an XCD.
-void place_items(std::vector<GroupItems> &groups, AttnPlan *plan) {
+void place_items(std::vector<GroupItems> &groups, int slots, AttnPlan *plan) {
   std::stable_sort(groups.begin(), groups.end(),
                    [](const GroupItems &x, const GroupItems &y) { return x.cost > y.cost; });
   std::vector<int64_t> load(kXcds, 0);
@@ -340,23 +400,45 @@ void place_items(std::vector<GroupItems> &groups, AttnPlan *plan) {
     load[x] += gi.cost;
     per_xcd[x].insert(per_xcd[x].end(), gi.items.begin(), gi.items.end());
   }
-  size_t max_len = 0;
-  int n_real = 0;
-  for (auto &v : per_xcd) {
-    // Longest items first; equal costs keep split-major order so that the
-    // workgroups resident together read the same key range.
-    // Longest by keys, narrow items too: ordered by their shorter time they
-    // ran bunched at the end, without the ordinary items' matrix work beside
-    // their loads (batch of 16 ragged conversations: 834 us a layer against
-    // 827, 40/8 heads P=32768, N=1024: 599 against 592; the HBM bytes do not
-    // differ).
-    std::stable_sort(v.begin(), v.end(), [](const WorkItem &x, const WorkItem &y) {
-      const int cx = x.k_end - x.k_begin, cy = y.k_end - y.k_begin;
+  // Longest by keys, equal ones in split-major order so that the workgroups
+  // resident together read the same key range.
+  auto keys_of = [](const WorkItem &w) -> int64_t { return w.k_end - w.k_begin; };
+  auto cost_of = [&](const WorkItem &w) {
+    return item_cost(w.k_end - w.k_begin, w.nq * plan->group, w.paged != 0, false, plan->narrow_rows);
+  };
+  auto sort_by = [](std::vector<WorkItem> &v, auto &&length) {
+    std::stable_sort(v.begin(), v.end(), [&](const WorkItem &x, const WorkItem &y) {
+      const int64_t cx = length(x), cy = length(y);
       if (cx != cy) return cx > cy;
       if (x.seq != y.seq) return x.seq < y.seq;
       if (x.split != y.split) return x.split < y.split;
       return x.q0 < y.q0;
     });
+  };
+  for (auto &v : per_xcd) sort_by(v, keys_of);
+  if (plan->narrow_rows > 0) {
+    // Narrow items have as many keys as their neighbours and take a third of
+    // the time.  Among these, where their loads run beside the ordinary
+    // items' matrix work, they do best (two full rounds, P=16384, N=410 of
+    // 40/8 heads: 134.5 us, 137.5 with the narrow items last; P=2048, N=1284
+    // of 32/8: 66.9 and 69.0), unless the schedule ends a twentieth or more
+    // later for it: then the long items go first (P=16384, N=107 of 40/8
+    // heads, 288 items: 56.7 us by keys, 45.1 by time).
+    std::vector<std::vector<WorkItem>> by_cost = per_xcd;
+    std::vector<int64_t> busy(busy_slots(slots));
+    int64_t span[2] = {0, 0};
+    for (int x = 0; x < kXcds; ++x) {
+      sort_by(by_cost[x], cost_of);
+      const std::vector<WorkItem> *lists[2] = {&per_xcd[x], &by_cost[x]};
+      for (int o = 0; o < 2; ++o)
+        span[o] = std::max(span[o], dispatch_span((int64_t)lists[o]->size(), slots / kXcds, busy.data(),
+                                                  [&](int64_t i) { return cost_of((*lists[o])[i]); }));
+    }
+    if (20 * span[1] <= 19 * span[0]) per_xcd.swap(by_cost);
+  }
+  size_t max_len = 0;
+  int n_real = 0;
+  for (auto &v : per_xcd) {
     max_len = std::max(max_len, v.size());
     n_real += (int)v.size();
   }
@@ -401,10 +483,7 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
   }
   plan->total_q = cq;
 
-  // Key-split choice: every sequence is split into chunks of at most `chunk`
-  // keys; try the chunk sizes that give 1..kMaxSplits splits to the longest
-  // sequence and keep the one with the shortest simulated schedule.  The
-  // keys read in place from the regular cache [0, rc) and the keys of the
+  // The keys read in place from the regular cache [0, rc) and the keys of the
   // active slot [rc, keys) never share an item.
   struct Range {
     int32_t k_begin, k_end, paged;
@@ -439,61 +518,36 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
     split_counts(chunk, b, &s_rc, &s_sl);
     return s_rc + s_sl;
   };
-  bool tail = false;
+  bool tail = false, matters[3] = {true, false, false};
   for (int b = 0; b < batch; ++b) {
-    const int n_qt = (N[b] + rows_q - 1) / rows_q;
-    tail = tail || narrow_tail(n_qt, (N[b] - (n_qt - 1) * rows_q) * group);
+    const int n_qt = (N[b] + rows_q - 1) / rows_q, last_rows = (N[b] - (n_qt - 1) * rows_q) * group;
+    tail = tail || narrow_tail(n_qt, last_rows);
+    for (int c = 1; c < 3; ++c)
+      matters[c] = matters[c] || (n_qt > 0 && narrow_matters(c, last_rows, rows_q * group, n_qt > 1));
   }
-  auto choose = [&](const SplitRule &rule, SplitChoice *out) {
-    int64_t best_span = -1;
-    size_t best_items = 0;
-    out->chunk = std::max<int64_t>(max_kv, 1);
-    for (int choice : kNarrowOrder[tail]) {
-      if (choice >= rule.n_narrow) continue;
-      const int narrow_rows = kNarrowChoices[choice];
-      bool matters = false;
-      for (int b = 0; b < batch && !matters; ++b) {
-        const int n_qt = (N[b] + rows_q - 1) / rows_q;
-        matters = n_qt > 0 && narrow_matters(choice, (N[b] - (n_qt - 1) * rows_q) * group, rows_q * group, n_qt > 1);
-      }
-      if (!matters) continue;
-      for (int s = 1; s <= rule.max_splits && !tiles.empty(); ++s) {
-        int64_t chunk = (max_kv + s - 1) / s;
-        chunk = ((chunk + kAttnKeyTile - 1) / kAttnKeyTile) * kAttnKeyTile;
-        if (s > 1 && chunk < kMinSplitKeys) break;
-        if (s > kManySplits && (int64_t)tiles.size() * s > slots) break;
-        std::vector<int64_t> costs;   // of one KV head's items; the others' are the same
-        std::vector<Range> rs;
-        for (const TileDesc &t : tiles) {
-          if (t.kvh != 0) continue;
-          ranges_for(chunk, t.seq, t.keys, &rs);
-          const int S = (int)rs.size();
-          for (const Range &r : rs)
-            costs.push_back(item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, S > 1, narrow_rows));
-        }
-        const size_t n = costs.size() * (size_t)n_kv_heads;
-        int64_t row_splits = 0;
-        for (int b = 0; b < batch; ++b) {
-          const int S = splits_for(chunk, b);
-          if (S > 1) row_splits += (int64_t)N[b] * n_q_heads * (S + 1);
-        }
-        const int64_t merge = row_splits > 0 ? rule.merge_launch_keys + row_splits / kMergeRowSplitsPerKey +
-                                                   (s > kManySplits ? kManySplitsKeys : 0)
-                                             : 0;
-        const int64_t extra = merge + kItemSharedKeys * (int64_t)n;
-        if (best_span >= 0 && span_bound(costs.data(), costs.size(), n_kv_heads, slots) + extra > best_span) continue;
-        const size_t one = costs.size();
-        costs.resize(n);
-        for (size_t i = one; i < n; ++i) costs[i] = costs[i - one];
-        const int64_t span = lpt_makespan(costs, slots) + extra;
-        if (best_span < 0 || span < best_span || (span == best_span && n < best_items)) {
-          best_span = span;
-          best_items = n;
-          out->chunk = chunk;
-          out->narrow_rows = narrow_rows;
-        }
-      }
+  std::vector<int64_t> costs(tiles.size() / std::max(1, n_kv_heads) * kMaxSplits), busy(busy_slots(slots));
+  std::vector<Range> rs;
+  auto costs_of = [&](int64_t chunk, int narrow_rows, int64_t *to) -> int64_t {
+    int64_t n = 0;
+    for (const TileDesc &t : tiles) {
+      if (t.kvh != 0) continue;
+      ranges_for(chunk, t.seq, t.keys, &rs);
+      for (const Range &r : rs)
+        to[n++] = item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, rs.size() > 1, narrow_rows);
     }
+    return n;
+  };
+  auto row_splits = [&](int64_t chunk) {
+    int64_t n = 0;
+    for (int b = 0; b < batch; ++b) {
+      const int S = splits_for(chunk, b);
+      if (S > 1) n += (int64_t)N[b] * n_q_heads * (S + 1);
+    }
+    return n;
+  };
+  auto choose = [&](const SplitRule &rule, SplitChoice *out) {
+    choose_splits(rule, max_kv, (int64_t)tiles.size(), n_kv_heads, std::max(1, slots), tail, matters,
+                  SplitScratch{costs.data(), busy.data()}, costs_of, row_splits, out);
     out->splits = batch > 0 ? splits_for(out->chunk, 0) : 1;
     return true;
   };
@@ -518,7 +572,6 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
   for (int b = 0; b < batch; ++b) {
     for (int g = 0; g < n_kv_heads; ++g) {
       GroupItems gi;
-      std::vector<Range> rs;
       for (; ti < tiles.size() && tiles[ti].seq == b && tiles[ti].kvh == g; ++ti) {
         const TileDesc &t = tiles[ti];
         ranges_for(best_chunk, b, t.keys, &rs);
@@ -539,11 +592,11 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
       if (!gi.items.empty()) groups.push_back(std::move(gi));
     }
   }
-  place_items(groups, plan);
   bool narrow = false;
-  for (const WorkItem &w : plan->items)
-    narrow = narrow || (w.seq >= 0 && !w.paged && w.nq * group <= plan->narrow_rows);
+  for (const GroupItems &gi : groups)
+    for (const WorkItem &w : gi.items) narrow = narrow || (!w.paged && w.nq * group <= plan->narrow_rows);
   if (!narrow) plan->narrow_rows = 0;
+  place_items(groups, slots, plan);
 }
 
 namespace {

@@ -454,6 +454,49 @@ def _plain_splits(P, N, hq, hkv, slots):
     return best[2]
 
 
+def _dispatched_span(items, group, narrow_rows, slots):
+    """Keys' worth of time of a plan's items as the dispatchers hand them out:
+    slot w to XCD w % 8, within an XCD to its four shader engines in turn,
+    never passing over one whose CUs are all busy."""
+    end = 0
+    for x in range(8):
+        engines = [[0] * (slots // 32) for _ in range(4)]
+        now = i = 0
+        for seq, _, _, nq, kb, ke, _, paged in items[x::8].tolist():
+            if seq < 0:
+                continue
+            keys = ke - kb
+            if nq * group <= narrow_rows and not paged:
+                keys = (55 if nq * group <= 32 else 110) + -(-keys // 128) * 44
+            engine = engines[i % 4]
+            now, i = max(now, engine[0]), i + 1
+            heapq.heapreplace(engine, now + keys + 192)
+            end = max(end, now + keys + 192)
+    return end
+
+
+# More items than CUs, some of them narrow tails: a few more than one or two
+# rounds (long ranges first), whole rounds, tails left over by the engines.
+@pytest.mark.parametrize("P,N,hq,hkv", [
+    (16384, 107, 40, 8), (16384, 133, 32, 8), (16384, 193, 32, 8), (16384, 613, 40, 8), (16384, 512, 40, 8),
+    (60000, 392, 32, 8), (8192, 261, 32, 8), (16384, 181, 28, 4), (16384, 410, 40, 8), (2048, 1284, 32, 8)])
+def test_planned_schedule_is_the_one_the_items_run_in(sc, P, N, hq, hkv):
+    """A plan with narrow items, run in its order, is no slower than the
+    plainest one (ordinary items, longest first) by more than a twentieth."""
+    items, splits = sc.sc_attn_plan_query([P], [N], hq, hkv, 256)
+    narrow, _ = sc.sc_attn_plan_kinds([P], [N], hq, hkv, 128, 256)
+    merge = lambda S: 120 + N * hq * (S + 1) // 600 if S > 1 else 0
+    span = _dispatched_span(items, hq // hkv, narrow, 256) + merge(splits[0])
+    S = _plain_splits(P, N, hq, hkv, 256)
+    lists = [sorted((i for i in _implicit_items(P, N, hq, hkv, S) if i[1] % 8 == x), key=lambda i: i[4] - i[5])
+             for x in range(8)]                                             # a KV head per XCD, longest first
+    plain = np.full((8 * max(map(len, lists)), 8), -1)
+    for x, v in enumerate(lists):
+        for i, it in enumerate(v):
+            plain[8 * i + x] = it
+    assert span <= 1.05 * (_dispatched_span(plain, hq // hkv, 0, 256) + merge(S)), (splits, S, narrow)
+
+
 def test_noalloc_takes_every_call_the_plainest_splits_fit(sc):
     """The allocation-free entry point refuses a call whose key splits need
     more partials than its array holds.  Whatever the planner likes better,
