@@ -57,7 +57,7 @@ ROTATE_BYTES = 512 << 20         # destination buffers the standalone fetch cycl
 PMC_TRAFFIC = {
     "llama3-8b-P8192-N512": (80613036, "c0550f556e52ba7d"),
     "llama3-8b-batch16-varlen": (844585662, "c0550f556e52ba7d"),
-    "qwen-14b-P32768-N1024": (526772008, "c0550f556e52ba7d"),
+    "qwen-14b-P32768-N1024": (364129361, "c0550f556e52ba7d"),
     "llama3-8b-P131072-N2048-hosttier": (1190699461, "c0550f556e52ba7d"),
     "llama3-8b-P8192-N512-rc0.5": (79977569, "c0550f556e52ba7d"),
 }

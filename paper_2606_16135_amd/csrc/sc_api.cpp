@@ -104,10 +104,15 @@ constexpr int64_t kNarrowKeys = 4 * kAttnKeyTile;
 constexpr int64_t kNarrowIterationKeys = 44;
 constexpr int64_t kNarrowOverheadKeys[2] = {55, 110};
 // The widest items a plan runs narrow: none, those of one row block, or of
-// two.  On a tie none, unless a longer turn's tail tile has one row block: it
-// rarely sets the schedule's length, but narrow it takes a third of the time
-// and leaves the rest of the chip its bandwidth and power (256 tokens of
-// 40/8 heads at P=16384, whose sixth tile has 5 rows: 86.5 us against 91.5).
+// two.  On a tie none, unless all items run at once and a longer turn's tail
+// tile has one row block: it rarely sets that schedule's length, but narrow
+// it takes a third of the time and leaves the rest of the chip its bandwidth
+// and power (256 tokens of 40/8 heads at P=16384, whose sixth tile has 5
+// rows: 86.5 us against 91.5).  In several rounds a tail that the schedule
+// gains nothing from costs bytes: its keys are read far from its neighbours'
+// reads of them (40/8 heads, P=32768, N=1024, 504 items: 364 -> 527 MB from
+// HBM and the same time, 577 us against 579; its stack of 4 layers 2523 and
+// 2517).
 // Narrow for nothing costs: a batch of 16-19 tokens a sequence 39.3 us a
 // layer against 38.2, a 16-layer stack of 15 short turns over half-regular
 // caches 907 us against 890.
@@ -124,6 +129,17 @@ int64_t item_cost(int64_t keys, int rows, bool paged, bool split, int narrow_row
   else
     c += keys;
   return c;
+}
+
+// A plan with narrow items runs its ordinary ones in the kernel that has
+// both, whose loads into LDS take a 200th longer (0.5-1.5%, attn_fwd.hip).
+// Their keys are counted for that: the longest item's, and the sum.  Priced
+// at a 50th instead, 50 drawn plans of several rounds took 0.1% longer.
+constexpr int64_t kNarrowKernelKeys = 200;
+void count_wide(int64_t keys, int rows, bool paged, int narrow_rows, int64_t (&wide)[2]) {
+  if (rows <= narrow_rows && !paged) return;
+  wide[0] = std::max(wide[0], keys);
+  wide[1] += keys;
 }
 
 // Whether a plan needs to consider this choice: some tile's rows fall
@@ -262,10 +278,14 @@ bool choose_splits(const SplitRule &rule, int64_t max_kv, int64_t n_tiles, int h
       if (s > 1 && chunk < kMinSplitKeys) break;
       if (s > kManySplits && n_tiles * s > slots) break;
       int64_t *const costs = scratch.costs;
-      const int64_t one = costs_of(chunk, narrow_rows, costs);
+      int64_t wide[2] = {0, 0};   // keys of ordinary items: the most, and all of a KV head's
+      const int64_t one = costs_of(chunk, narrow_rows, costs, wide);
       if (one < 0) return false;
       const int64_t n = one * hkv, rows = row_splits(chunk);
-      const int64_t extra = kItemSharedKeys * n +
+      const bool tie_narrow = tail && n <= slots;   // see kNarrowChoices
+      const int64_t slower = choice == 0 || tie_narrow ? 0
+                             : (std::max(wide[0], wide[1] * hkv / slots) + kNarrowKernelKeys - 1) / kNarrowKernelKeys;
+      const int64_t extra = kItemSharedKeys * n + slower +
                             (rows > 0 ? rule.merge_launch_keys + rows / kMergeRowSplitsPerKey +
                                             (s > kManySplits ? kManySplitsKeys : 0)
                                       : 0);
@@ -311,7 +331,7 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, cons
   const int last_rows = n_qt > 0 ? (N - (n_qt - 1) * rows_q) * group : 0;
   bool matters[3];
   for (int c = 0; c < 3; ++c) matters[c] = narrow_matters(c, last_rows, rows_q * group, n_qt > 1);
-  auto costs_of = [&](int64_t chunk, int narrow_rows, int64_t *to) -> int64_t {
+  auto costs_of = [&](int64_t chunk, int narrow_rows, int64_t *to, int64_t (&wide)[2]) -> int64_t {
     const int S = splits_of(chunk);
     if ((int64_t)n_qt * S > kNoAllocMaxCosts) return -1;
     int64_t n = 0;
@@ -322,7 +342,9 @@ static bool choose_splits_noalloc(int P, int N, int hq, int hkv, int slots, cons
       for (int sp = 0; sp < S; ++sp) {
         const int b0 = std::min(keys, (int)((int64_t)sp * t / S) * kAttnKeyTile);
         const int b1 = std::min(keys, (int)((int64_t)(sp + 1) * t / S) * kAttnKeyTile);
-        to[n++] = item_cost(std::max(b0, b1) - b0, std::min(rows_q, N - q0) * group, false, S > 1, narrow_rows);
+        const int rows = std::min(rows_q, N - q0) * group;
+        to[n++] = item_cost(std::max(b0, b1) - b0, rows, false, S > 1, narrow_rows);
+        count_wide(std::max(b0, b1) - b0, rows, false, narrow_rows, wide);
       }
     }
     return n;
@@ -527,13 +549,15 @@ void plan_attention(const std::vector<int32_t> &P, const std::vector<int32_t> &N
   }
   std::vector<int64_t> costs(tiles.size() / std::max(1, n_kv_heads) * kMaxSplits), busy(busy_slots(slots));
   std::vector<Range> rs;
-  auto costs_of = [&](int64_t chunk, int narrow_rows, int64_t *to) -> int64_t {
+  auto costs_of = [&](int64_t chunk, int narrow_rows, int64_t *to, int64_t (&wide)[2]) -> int64_t {
     int64_t n = 0;
     for (const TileDesc &t : tiles) {
       if (t.kvh != 0) continue;
       ranges_for(chunk, t.seq, t.keys, &rs);
-      for (const Range &r : rs)
+      for (const Range &r : rs) {
         to[n++] = item_cost(r.k_end - r.k_begin, t.nq * group, r.paged != 0, rs.size() > 1, narrow_rows);
+        count_wide(r.k_end - r.k_begin, t.nq * group, r.paged != 0, narrow_rows, wide);
+      }
     }
     return n;
   };

@@ -497,6 +497,20 @@ def test_planned_schedule_is_the_one_the_items_run_in(sc, P, N, hq, hkv):
     assert span <= 1.05 * (_dispatched_span(plain, hq // hkv, 0, 256) + merge(S)), (splits, S, narrow)
 
 
+@pytest.mark.parametrize("P,N,hq,hkv,narrow", [
+    (32768, 1024, 40, 8, 0), (16943, 1018, 48, 8, 0), (16384, 1018, 48, 8, 0),    # several rounds: no gain
+    (16384, 256, 40, 8, 32),                                                    # all items at once
+    (16384, 107, 40, 8, 32), (16384, 512, 40, 8, 32), (10914, 819, 8, 8, 64)])   # shorter by it
+def test_tails_run_narrow_only_where_they_gain(sc, P, N, hq, hkv, narrow):
+    """A long turn's tail tile runs narrow where all items run at once or the
+    schedule gains by it.  Elsewhere it reads its keys from memory once more
+    and puts every item into the kernel that has both kinds."""
+    items, _ = sc.sc_attn_plan_query([P], [N], hq, hkv, 256)
+    tails = items[(items[:, 0] >= 0) & (items[:, 3] * (hq // hkv) <= 64)]
+    assert len(tails) > 0
+    assert sc.sc_attn_plan_kinds([P], [N], hq, hkv, 128, 256)[0] == narrow
+
+
 def test_noalloc_takes_every_call_the_plainest_splits_fit(sc):
     """The allocation-free entry point refuses a call whose key splits need
     more partials than its array holds.  Whatever the planner likes better,
