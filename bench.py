@@ -55,11 +55,11 @@ ROTATE_BYTES = 512 << 20         # destination buffers the standalone fetch cycl
 # with the hash of the attention source's code (comments left out) they were
 # taken on; a stale entry (the code changed since) is reported as null.
 PMC_TRAFFIC = {
-    "llama3-8b-P8192-N512": (80613036, "c0550f556e52ba7d"),
-    "llama3-8b-batch16-varlen": (844585662, "c0550f556e52ba7d"),
-    "qwen-14b-P32768-N1024": (364129361, "c0550f556e52ba7d"),
-    "llama3-8b-P131072-N2048-hosttier": (1190699461, "c0550f556e52ba7d"),
-    "llama3-8b-P8192-N512-rc0.5": (79977569, "c0550f556e52ba7d"),
+    "llama3-8b-P8192-N512": (80649182, "05ad5acc2aef4c49"),
+    "llama3-8b-batch16-varlen": (843236082, "05ad5acc2aef4c49"),
+    "qwen-14b-P32768-N1024": (364168443, "05ad5acc2aef4c49"),
+    "llama3-8b-P131072-N2048-hosttier": (1191082167, "05ad5acc2aef4c49"),
+    "llama3-8b-P8192-N512-rc0.5": (79994037, "05ad5acc2aef4c49"),
 }
 
 

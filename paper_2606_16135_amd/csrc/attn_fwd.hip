@@ -628,10 +628,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     vw[3] = __builtin_bit_cast(u32x2, hi)[1];
     return vw;
   };
-  // O^T += V^T . P^T.
-  auto pv = [&](const unsigned char *slot, const u32x4 (&pfp)[2 * NB]) {
+  // O^T += V^T . P^T over the tile's first 16 steps keys.
+  auto pv = [&](const unsigned char *slot, const u32x4 (&pfp)[2 * NB], auto steps) {
 #pragma unroll
-    for (int t = 0; t < 2 * NB; ++t)
+    for (int t = 0; t < decltype(steps)::value; ++t)
 #pragma unroll
       for (int c = 0; c < D / 32; ++c) w.oacc[c] = Elem<DT>::mfma(v_operand(slot, t, c), pfp[t], w.oacc[c]);
   };
@@ -806,11 +806,49 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
         bk1 = bn1;
       }
     };
+    // The last tile of a range at head_dim 64 whose second 32-key block has no
+    // keys: PV(j-1) and the first block's softmax, no QK, no loads, and the
+    // first block's PV, in the order of a whole tile (the same bits).  Taken
+    // as a whole one, whose second half is masked, it cost every range of an
+    // odd number of blocks 0.3-0.6 us, and calls over few keys had become
+    // slower than with 32-key tiles: 8/8 heads, P=71, N=2 5.65 us, 5.36 so
+    // (5.26 with 32-key tiles); 32/8, P=814, N=18 9.61, 9.04 (9.02); 113
+    // drawn calls at head_dim 64 2.2% faster in the mean.
+    auto iterate_half = [&](auto j_tag, auto first_tag, int j) {
+      constexpr int J = decltype(j_tag)::value;
+      constexpr bool kFirst = decltype(first_tag)::value;
+      constexpr int PAR = J & 1;
+      f32x16 (&sc)[1] = reinterpret_cast<f32x16 (&)[1]>(w.s[PAR]);
+      u32x4 (&pf)[2] = reinterpret_cast<u32x4 (&)[2]>(w.pfb[PAR]);
+      apply_mask(sc, lim_of(j));
+      if constexpr (kFirst) {
+        const float tm = tile_max(sc, sl2);
+        w.m_run = tm > -INFINITY ? tm : 0.f;
+      } else {
+        pv(v_slot(SC_IC(J + R - 1)), w.pfb[PAR ^ 1], SC_IC(2 * NB));
+      }
+      float rs = softmax_tile<DT>(sc, pf, sl2, w.m_run);
+      if (!kFirst && __builtin_amdgcn_ballot_w64(!(rs <= Elem<DT>::kSumLimit))) {
+        w.s[PAR][NB - 1] = f32x16{} - INFINITY;
+        rs = settle_max<D, DT>(w, w.s[PAR], w.pfb[PAR], sl2);
+      }
+      w.l_run += rs;
+      if constexpr (PAR == 1) dma_barrier<0>();
+      pv(v_slot(SC_IC(J)), w.pfb[PAR], SC_IC(2));
+    };
     // j = 0 .. R-1 masked (exact for any tile; j = 0 sets the reference
     // max), then whole rounds of R unmasked tiles, then the rest masked.
-    iterate(std::integral_constant<int, 0>(), T(), T(), 0);
+    constexpr bool kHalves = KG == 1 && NB == 2;
+    const auto half_last = [&] {
+      if constexpr (kHalves)
+        return k_end - k_begin - (n - 1) * TK <= TK / 2;
+      else
+        return F();
+    }();
+    const int n_full = n_it - half_last;
+    if (!kHalves || n_full > 0) iterate(std::integral_constant<int, 0>(), T(), T(), 0);
     static_for<1, R>([&](auto J) {
-      if (decltype(J)::value < n_it) iterate(J, T(), F(), decltype(J)::value);
+      if (decltype(J)::value < (kHalves ? n_full : n_it)) iterate(J, T(), F(), decltype(J)::value);
     });
     int j = R;
     const int jm = min(j_mask, n_it);
@@ -819,15 +857,25 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring
     // for a copy workgroup beside them.)
     if constexpr (KG == 1 || D == 128)
       for (; j + R - 1 < jm; j += R) static_for<0, R>([&](auto J) { iterate(J, F(), F(), j + decltype(J)::value); });
-    for (; j < n_it; j += R)
+    for (; j < n_full; j += R)
       static_for<0, R>([&](auto J) {
-        if (j + decltype(J)::value < n_it) iterate(J, T(), F(), j + decltype(J)::value);
+        if (j + decltype(J)::value < n_full) iterate(J, T(), F(), j + decltype(J)::value);
       });
     // PV of the last tile; its V landed before the last barrier.
     const int last = (n_it - 1) % R;
     static_for<0, R>([&](auto S) {
-      constexpr int kS = decltype(S)::value;
-      if (last == kS) pv(v_slot(S), w.pfb[kS & 1]);   // R is even: kS has the parity of n_it - 1
+      constexpr int kS = decltype(S)::value;   // R is even: kS has the parity of n_it - 1
+      if (last != kS) return;
+      if constexpr (kHalves) {
+        if (half_last) {
+          if (kS == 0 && n_full == 0)
+            iterate_half(S, T(), 0);
+          else
+            iterate_half(S, F(), n_full);
+          return;
+        }
+      }
+      pv(v_slot(S), w.pfb[kS & 1], SC_IC(2 * NB));
     });
     // Loads of tiles past the end may still be in flight.
     dma_wait_all();

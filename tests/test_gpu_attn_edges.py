@@ -50,6 +50,35 @@ def test_key_counts_around_tile_edges(d, dtype):
             _single(sc, keys - n, n, 8, 2, d, dtype, 100 * i + n)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("keys", [20, 32, 65, 90, 96, 150, 215, 280, 345, 410])
+def test_reference_moves_in_half_a_tile(keys, dtype):
+    """Unsplit calls at head_dim 64 whose last tile has keys in its first
+    half only; one of those keys leaves the safe range of one row's sum."""
+    sc = require_gpu()
+    import torch
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    n, hq, hkv, d = 20, 128, 32, 64
+    p = keys - n
+    spike = (keys - 1) // 64 * 64                 # first key of the last tile
+    assert sc.sc_attn_plan_query([p], [n], hq, hkv)[1] == [1] and keys - spike <= 32
+    assert sc.sc_attn_plan_kinds([p], [n], hq, hkv, d)[0] == 0
+    print(f"[half tile] keys={keys} N={n} heads {hq}/{hkv} {dtype}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(keys)
+    q = (4 * torch.randn((n, hq, d), generator=g, device="cuda")).to(td)
+    k = torch.randn((keys, hkv, d), generator=g, device="cuda").to(td)
+    v = torch.randn((keys, hkv, d), generator=g, device="cuda").to(td)
+    k[spike] = (q[n - 1, ::hq // hkv].float() * 0.75).to(td)
+    out = torch.full((n, hq, d), float("nan"), dtype=td, device="cuda")
+    f = sc.sc_prefill_attn if dtype == "bf16" else sc.sc_prefill_attn_f16
+    f(q.data_ptr(), k.data_ptr(), v.data_ptr(), p, n, hq, hkv, d, out.data_ptr(),
+      stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    ref, _ = oa.attention(*(bits_to_f64(to_u16(t), dtype) for t in (q, k, v)), [p], [n])
+    compare_attention(to_u16(out), ref, f"keys={keys}", dtype)
+
+
 def test_longest_sequence_head_dim_64():
     """2 GiB of keys less 256 tokens at 8 KV heads x 64 dims: tiles of 64
     keys past the last one would start beyond the signed 32-bit offsets."""
