@@ -395,11 +395,11 @@ __device__ __forceinline__ void store_row(const WaveState<D> &w, float inv, int 
 // runs its 256 rows' worth of MFMAs whatever it holds; a narrow one takes a
 // third to a quarter of the time per key, plus 1.7 us (3.4 with two row
 // blocks) for its start and the combination.  Calls of 32/8 heads, ordinary
-// against narrow: P=8192, N=1 15.6 -> 13.8 us, P=32768, N=8 36.3 -> 33.5,
-// P=2048, N=8 11.4 -> 10.1, P=256, N=4 8.5 -> 6.9 (one split, no merge);
+// against narrow: P=8192, N=1 16.0 -> 12.3 us, P=32768, N=8 33.5 -> 28.0,
+// P=2048, N=8 11.5 -> 9.8, P=256, N=4 9.6 -> 6.6 (one split, no merge);
 // layer stack of 40/8 heads in chunks of 256 tokens, whose last query tile
-// has 5 rows: 1610 -> 1540 us.  The kinds are separate copies of the whole body so that each is register-allocated on
-// its own.
+// has 5 rows: 1633 -> 1590 us.  The kinds are separate copies of the whole
+// body so that each is register-allocated on its own.
 template <int D, int DT, bool kPaged, int KG, bool kNamed>
 __device__ __forceinline__ void attn_item(const AttnArgs &a, unsigned char *ring, const WorkItem &wi, const SeqDesc &sd) {
   static_assert(KG == 1 || (KG == kNarrowGroups && !kPaged && !kNamed), "kinds of item");

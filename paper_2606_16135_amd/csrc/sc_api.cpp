@@ -64,42 +64,48 @@ constexpr int kMaxSplits = kAttnMaxSplits;
 // More splits than this only where they still run in one round of
 // workgroups, i.e. for the fewest query tiles: a turn of at most 256 / group
 // tokens has one per KV head, and with 8 KV heads 16 splits leave half of
-// the CUs idle.  fp16 call of 40/8 heads, P=32768, N=48: 57.0 us with 16
-// splits, 46.2 with the 32 chosen now; P=32768, N=8 of 32/8 heads 51 -> 39,
-// P=8192, N=1 18.8 -> 15.9, P=4096, N=16 unchanged (14.7).  With more tiles
+// the CUs idle.  fp16 call of 40/8 heads, P=32768, N=48: 55.1 us with 16
+// splits, 45.3 with the 32 chosen; ordinary items of P=8192, N=1, 32/8 heads
+// 18.8 and 16.3.  Narrow items, which such turns mostly run, gain less: P=32768,
+// N=8 29.2 us with 16 splits and 28.1 with the 29 chosen.  With more tiles
 // the extra partials only add rounds and merge traffic (P=3000, N=100:
 // 11 splits 21 us, 20 splits 60).
 constexpr int kManySplits = 16;
 // ... and where they save more than the wider merge costs (about 1.5 us:
-// 28/4 heads, P=3475, N=32: 16.7 us with 16 splits, 17.2 with 22).
+// 28/4 heads, P=3475, N=32: 16.1 us with 16 splits, 17.0 with 22).
 constexpr int64_t kManySplitsKeys = 45;
 constexpr int kResidentPerCu = 1;        // one 8-wave workgroup per CU (LDS ring, 2 waves per SIMD)
 constexpr int kQueryDefaultSlots = 256 * kResidentPerCu;   // MI355X: 256 CUs
 constexpr int64_t kItemOverheadKeys = 128;  // prologue + epilogue, in keys
 constexpr int64_t kMergeOverheadKeys = 64;  // partial write of a split item, in keys
 // The merge kernel runs after the forward kernel, so its time adds to the
-// schedule: a launch plus a term proportional to the partial rows it reads
-// and the output rows it writes.  Calibrated on MI355X, where a key of one
-// workgroup's range costs ~33 ns: the 8B shape's merge (16384 rows, 4
-// splits) takes ~5.8 us, the 16-conversation batch's (~520k row-splits)
-// ~33 us.
+// schedule: a fixed part plus a term proportional to the partial rows it
+// reads and the output rows it writes, in keys of about 33 ns.  The fixed part
+// is what a split adds to a short call beside the merge's work: the second
+// launch and the gap before it, about 4 us.  (The merge kernel alone takes 4
+// us for 1024 rows, 5.8 for the 8B shape's 16384 x 4 splits and 33 for a
+// 16-conversation batch's 520k row-splits, so long merges are priced up to a
+// half too high; a long call's splits hardly depend on it.)  400 drawn calls
+// take 0.2% longer in the mean at 95 keys, 0.25% at 70 and 0.8% at 45, though
+// some of the shortest are faster split: 8/8 heads of 64, P=158, N=101 8.8 us
+// unsplit, 8.1 with 5 splits.
 constexpr int64_t kMergeLaunchKeys = 120;
 constexpr int64_t kMergeRowSplitsPerKey = 600;  // (rows x (splits + 1)) per key of merge time
 // Every item also reads its Q tile and writes its output or partial tile
 // (256 rows each way, 128 KiB at head_dim 128), and that traffic shares HBM
-// with every other item in flight: about 30 ns, one key, per item.  With
-// this term and two-tile splits allowed, the split count chosen for 21
-// single-sequence shapes (P 256..32768, N 16..1024, 32 or 40 query heads)
-// came within 2% of the fastest of 1..16 splits measured on MI355X for each;
-// short turns (P <= 4096, N <= 256) run 10-35% faster than with a 512-key
-// floor and no such term.
+// with every other item in flight: about 30 ns, one key, per item.  With all
+// these terms the split count chosen for 18 of 21 single-sequence shapes (P
+// 256..32768, N 16..1024, 32 or 40 query heads) is within 2% of the fastest
+// of 1..16 (one query tile: ..32) splits forced on MI355X; P=256, N=16 and 64
+// run unsplit, 6 and 4% over 7 and 6 splits, P=8192, N=64 takes 26 splits, 5%
+// over 20.
 constexpr int64_t kItemSharedKeys = 1;
 // A narrow item (few rows, see attn_item) takes 128 keys in an iteration
 // that costs about 1.4 of an ordinary one's 32, and pays for the start of
 // four tiles at once and the combination of its key groups: about 1.7 us
 // with one row block, 3.4 with two (P=1024, N=16 of 32/8 heads, 64 rows:
-// 10.5 us with ordinary items, 11.7 narrow; P=2048, N=8, 32 rows: 11.4 and
-// 10.0).
+// 10.3 us with ordinary items, 11.7 narrow; P=2048, N=8, 32 rows: 11.5 and
+// 9.8).
 constexpr int64_t kNarrowKeys = 4 * kAttnKeyTile;
 constexpr int64_t kNarrowIterationKeys = 44;
 constexpr int64_t kNarrowOverheadKeys[2] = {55, 110};
