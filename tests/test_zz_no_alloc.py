@@ -65,6 +65,32 @@ def test_noalloc_matches_allocating_entry_point_on_successive_calls():
         pytest.fail("expected at least two calls")
 
 
+# Calls with narrow items: one and two row blocks, unsplit and split, tails of
+# longer turns in one and in several rounds.  (P, N, Hq, Hkv, D, narrow rows)
+NARROW = [(500, 8, 8, 2, 128, 32), (368, 16, 8, 2, 64, 64), (4000, 16, 8, 2, 128, 64), (9000, 3, 32, 8, 64, 32),
+          (16384, 256, 40, 8, 128, 32), (16384, 107, 40, 8, 128, 32), (10914, 819, 8, 8, 64, 64)]
+
+
+@pytest.mark.parametrize("P,N,hq,hkv,d,narrow", NARROW)
+def test_noalloc_runs_narrow_items_like_the_allocating_entry_point(P, N, hq, hkv, d, narrow):
+    sc = require_gpu()
+    import torch
+
+    assert sc.sc_attn_plan_kinds([P], [N], hq, hkv, d)[0] == narrow
+    assert sc.sc_attn_noalloc_narrow_rows(P, N, hq, hkv) == narrow
+    print(f"\n[noalloc] narrow items: P={P} N={N} heads {hq}/{hkv} D={d}", flush=True)
+    stream = torch.cuda.current_stream().cuda_stream
+    q, k, v = _inputs(torch, P, N, hq, hkv, d, 2606_16135_970 + N)
+    outs = [torch.full((N, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    lses = [torch.full((hq, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for f, out, lse in zip((sc.sc_prefill_attn, sc.sc_prefill_attn_noalloc), outs, lses):
+        f(q.data_ptr(), k.data_ptr(), v.data_ptr(), P, N, hq, hkv, d, out.data_ptr(), lse=lse.data_ptr(),
+          stream=stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_u16(outs[0]), to_u16(outs[1]))
+    assert np.array_equal(lses[0].cpu().numpy().view(np.uint32), lses[1].cpu().numpy().view(np.uint32))
+
+
 def test_noalloc_takes_a_call_its_array_would_not_hold_at_more_splits():
     """Turns whose cheapest schedule has more key splits than the array
     holds run with fewer, like sc_prefill_attn's."""
